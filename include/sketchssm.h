@@ -246,6 +246,33 @@ int sketchssm_decode(const skssm_config* cfg, const void* U, const float* coef, 
 int sketchssm_full_read_baseline(const skssm_config* cfg, const float* S, const skssm_ring* ring,
                                  int32_t n_buffered, const void* q, float* o, void* stream);
 
+/* The raw update inputs of one token in arrays of their own, one token for
+ * every item: what a producer that does not write the ring itself hands to
+ * sketchssm_step. */
+typedef struct {
+  const void* k;          /* [B][H][K] io_dtype                                   */
+  const void* v;          /* [B][H][V] io_dtype                                   */
+  const float* beta;      /* [B][H]                                               */
+  const float* log_decay; /* [B][H] (MAMBA2, GDN) or [B][H][K] (KDA), <= 0        */
+} skssm_token;
+
+/*
+ * sketchssm_step -- one token of Algorithm 1's loop in one launch: appends
+ * `token` to ring slot n_buffered (0..W-1; ring.k, .v, .beta and .log_decay of
+ * that slot are written) and reads it, as the call below would from the slot:
+ *   n_buffered = W-1  sketchssm_update (the flush; baseline != 0: at rank 0)
+ *   baseline != 0     sketchssm_full_read_baseline
+ *   otherwise         sketchssm_decode
+ * Results are bitwise those of writing the slot and making that call; the
+ * kernel takes the token from its own arrays and stores it beside its other
+ * work, so the append costs one write of the token and no launch.  Every
+ * other argument is that call's, with its requirements (those a call does not
+ * name may be NULL).  q, o and the token's arrays are required.
+ */
+int sketchssm_step(const skssm_config* cfg, int32_t baseline, float* S, const float* omega, const float* coef,
+                   const skssm_ring* ring, int32_t n_buffered, const skssm_token* token, const void* q, void* U,
+                   void* cmap, float* o, void* stream);
+
 /*
  * sketchssm_state_to_tiles / sketchssm_state_from_tiles -- convert states
  * between the row layout X[B][H][V][K] (X = S^T, K contiguous; how a caller

@@ -22,7 +22,7 @@ F32, BF16 = 0, 1
 STATUS = {0: "SKSSM_OK", -1: "SKSSM_EINVAL", -2: "SKSSM_EUNSUPPORTED", -3: "SKSSM_EALIGN",
           -4: "SKSSM_ESTATE", -5: "SKSSM_EHIP"}
 
-FUNCTIONS = ("sketchssm_update", "sketchssm_decode", "sketchssm_full_read_baseline",
+FUNCTIONS = ("sketchssm_update", "sketchssm_decode", "sketchssm_full_read_baseline", "sketchssm_step",
              "sketchssm_state_to_tiles", "sketchssm_state_from_tiles", "sketchssm_buffer_sizes",
              "sketchssm_ring_bytes", "sketchssm_status_string", "sketchssm_last_error", "sketchssm_check_config")
 
@@ -52,6 +52,10 @@ class Ring(ctypes.Structure):
                 ("k", "v", "beta", "log_decay", "f", "pi", "tinv")]
 
 
+class Token(ctypes.Structure):
+    _fields_ = [(name, ctypes.c_void_p) for name in ("k", "v", "beta", "log_decay")]
+
+
 _lib = None
 
 
@@ -70,9 +74,11 @@ def load(path: str | None = None):
     lib.sketchssm_update.argtypes = [cfgp, P, P, ringp, ctypes.c_int32, P, P, P, P, P]
     lib.sketchssm_decode.argtypes = [cfgp, P, P, P, P, ringp, ctypes.c_int32, P, P, P]
     lib.sketchssm_full_read_baseline.argtypes = [cfgp, P, ringp, ctypes.c_int32, P, P, P]
+    lib.sketchssm_step.argtypes = [cfgp, ctypes.c_int32, P, P, P, ringp, ctypes.c_int32, ctypes.POINTER(Token), P, P, P,
+                                   P, P]
     lib.sketchssm_state_to_tiles.argtypes = [cfgp, P, P, P]
     lib.sketchssm_state_from_tiles.argtypes = [cfgp, P, P, P]
-    for f in ("sketchssm_update", "sketchssm_decode", "sketchssm_full_read_baseline", "sketchssm_check_config",
+    for f in ("sketchssm_update", "sketchssm_decode", "sketchssm_full_read_baseline", "sketchssm_step", "sketchssm_check_config",
               "sketchssm_state_to_tiles", "sketchssm_state_from_tiles"):
         getattr(lib, f).restype = ctypes.c_int
     lib.sketchssm_check_config.argtypes = [cfgp]
@@ -192,6 +198,17 @@ def sketchssm_full_read_baseline(cfg: Config, S, ring: Ring, n_buffered: int, q,
     lib = load()
     _check(lib.sketchssm_full_read_baseline(ctypes.byref(cfg), ptr(S), ctypes.byref(ring) if ring else None,
                                             int(n_buffered), ptr(q), ptr(o), stream))
+
+
+def sketchssm_step(cfg: Config, baseline: bool, S, omega, coef, ring: Ring, n_buffered: int, k, v, beta, log_decay, q, U, o,
+                   stream=None, cmap=None):
+    """Append the token (k, v, beta, log_decay: its own arrays) to slot n_buffered and read it, in one launch."""
+    lib = load()
+    tok = Token(ptr(k), ptr(v), ptr(beta), ptr(log_decay))
+    rc = lib.sketchssm_step(cfg, 1 if baseline else 0, ptr(S), ptr(omega), ptr(coef), ring, n_buffered, tok, ptr(q), ptr(U),
+                            ptr(cmap), ptr(o), stream)
+    if rc:
+        _check(rc)
 
 
 def sketchssm_state_to_tiles(cfg: Config, S_rows, S, stream=None):

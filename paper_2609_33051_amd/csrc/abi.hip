@@ -134,6 +134,23 @@ int launched(int rc, const char* what) {
   return SKSSM_OK;
 }
 
+// The current token's own arrays (sketchssm_step): all required, aligned like
+// every pointer; `t` NULL (the other calls) leaves the arguments NULL.
+int check_token(const skssm_token* t) {
+  if (!t->k || !t->v || !t->beta || !t->log_decay) return fail(SKSSM_EINVAL, "token k/v/beta/log_decay is NULL");
+  if (!aligned(t->k) || !aligned(t->v) || !aligned(t->beta) || !aligned(t->log_decay))
+    return fail(SKSSM_EALIGN, "token array not 16-byte aligned");
+  return SKSSM_OK;
+}
+
+template <class A> void put_token(A& a, const skssm_token* t) {
+  if (!t) return;
+  a.tk = t->k;
+  a.tv = t->v;
+  a.tbeta = t->beta;
+  a.tla = t->log_decay;
+}
+
 skssm::DecodeArgs decode_args(const skssm_config* c, const skssm_ring* r, int32_t n, const void* q, float* o) {
   skssm::DecodeArgs a{};
   a.B = c->batch;
@@ -165,28 +182,8 @@ int state_layout(const skssm_config* cfg, const float* src, float* dst, void* st
   return launched(skssm::run_state_layout(src, dst, items, cfg->dk, cfg->dv, to_tiles, stream), what);
 }
 
-}  // namespace
-
-extern "C" {
-
-const char* sketchssm_status_string(int status) {
-  switch (status) {
-    case SKSSM_OK: return "ok";
-    case SKSSM_EINVAL: return "invalid argument";
-    case SKSSM_EUNSUPPORTED: return "unsupported shape";
-    case SKSSM_EALIGN: return "pointer not 16-byte aligned";
-    case SKSSM_ESTATE: return "n_buffered out of range";
-    case SKSSM_EHIP: return "HIP runtime error";
-    default: return "unknown status";
-  }
-}
-
-const char* sketchssm_last_error(void) { return g_err; }
-
-int sketchssm_check_config(const skssm_config* cfg) { return check_shape(cfg, true, false); }
-
-int sketchssm_update(const skssm_config* cfg, float* S, const float* omega, const skssm_ring* ring,
-                     int32_t n_buffered, const void* q, void* U, void* cmap, float* o, void* stream) {
+int update(const skssm_config* cfg, float* S, const float* omega, const skssm_ring* ring, int32_t n_buffered,
+           const skssm_token* token, const void* q, void* U, void* cmap, float* o, void* stream) {
   int rc = check_shape(cfg, true, true);
   if (rc) return rc;
   Ranks rk;
@@ -219,6 +216,8 @@ int sketchssm_update(const skssm_config* cfg, float* S, const float* omega, cons
       return fail(SKSSM_ESTATE, "n_buffered %d outside 0..%d", n_buffered, cfg->window - 1);
     if (!aligned(q)) return fail(SKSSM_EALIGN, "q not aligned");
     if ((rc = check_ring(cfg, ring, false, false))) return rc;
+    if (token && (rc = check_token(token))) return rc;
+    put_token(a, token);
     a.nt = n_buffered + 1;
     a.q = q;
     a.rk = ring->k;
@@ -246,8 +245,8 @@ int sketchssm_update(const skssm_config* cfg, float* S, const float* omega, cons
   return launched(r, "sketchssm_update");
 }
 
-int sketchssm_decode(const skssm_config* cfg, const void* U, const float* coef, const void* cmap, const float* S,
-                     const skssm_ring* ring, int32_t n_buffered, const void* q, float* o, void* stream) {
+int decode(const skssm_config* cfg, const void* U, const float* coef, const void* cmap, const float* S,
+           const skssm_ring* ring, int32_t n_buffered, const skssm_token* token, const void* q, float* o, void* stream) {
   int rc = check_shape(cfg, true, false);
   if (rc) return rc;
   Ranks rk;
@@ -269,7 +268,9 @@ int sketchssm_decode(const skssm_config* cfg, const void* U, const float* coef, 
     if (!aligned(S)) return fail(SKSSM_EALIGN, "S not aligned");
   }
   if ((rc = check_ring(cfg, ring, rk.sketched > 0, rk.dense > 0))) return rc;
+  if (token && (rc = check_token(token))) return rc;
   skssm::DecodeArgs a = decode_args(cfg, ring, n_buffered, q, o);
+  put_token(a, token);
   put_ranks(a, rk);
   put_order(a, rk);
   a.S = rk.dense ? S : nullptr;
@@ -285,8 +286,8 @@ int sketchssm_decode(const skssm_config* cfg, const void* U, const float* coef, 
   return launched(r, "sketchssm_decode");
 }
 
-int sketchssm_full_read_baseline(const skssm_config* cfg, const float* S, const skssm_ring* ring,
-                                 int32_t n_buffered, const void* q, float* o, void* stream) {
+int full_read(const skssm_config* cfg, const float* S, const skssm_ring* ring, int32_t n_buffered,
+              const skssm_token* token, const void* q, float* o, void* stream) {
   int rc = check_shape(cfg, false, false);
   if (rc) return rc;
   Ranks rk;
@@ -297,7 +298,9 @@ int sketchssm_full_read_baseline(const skssm_config* cfg, const float* S, const 
   if (!S || !o || !q) return fail(SKSSM_EINVAL, "S, q and o are required");
   if (!aligned(S) || !aligned(o) || !aligned(q)) return fail(SKSSM_EALIGN, "S/q/o not aligned");
   if ((rc = check_ring(cfg, ring, false, true))) return rc;
+  if (token && (rc = check_token(token))) return rc;
   skssm::DecodeArgs a = decode_args(cfg, ring, n_buffered, q, o);
+  put_token(a, token);
   a.S = S;
   int r;
   switch (cfg->kind) {
@@ -306,6 +309,55 @@ int sketchssm_full_read_baseline(const skssm_config* cfg, const float* S, const 
     default: r = skssm::run_full_read_kda(a, cfg->dk, cfg->dv, cfg->io_dtype, stream); break;
   }
   return launched(r, "sketchssm_full_read_baseline");
+}
+
+}  // namespace
+
+extern "C" {
+
+const char* sketchssm_status_string(int status) {
+  switch (status) {
+    case SKSSM_OK: return "ok";
+    case SKSSM_EINVAL: return "invalid argument";
+    case SKSSM_EUNSUPPORTED: return "unsupported shape";
+    case SKSSM_EALIGN: return "pointer not 16-byte aligned";
+    case SKSSM_ESTATE: return "n_buffered out of range";
+    case SKSSM_EHIP: return "HIP runtime error";
+    default: return "unknown status";
+  }
+}
+
+const char* sketchssm_last_error(void) { return g_err; }
+
+int sketchssm_check_config(const skssm_config* cfg) { return check_shape(cfg, true, false); }
+
+int sketchssm_update(const skssm_config* cfg, float* S, const float* omega, const skssm_ring* ring,
+                     int32_t n_buffered, const void* q, void* U, void* cmap, float* o, void* stream) {
+  return update(cfg, S, omega, ring, n_buffered, nullptr, q, U, cmap, o, stream);
+}
+
+int sketchssm_decode(const skssm_config* cfg, const void* U, const float* coef, const void* cmap, const float* S,
+                     const skssm_ring* ring, int32_t n_buffered, const void* q, float* o, void* stream) {
+  return decode(cfg, U, coef, cmap, S, ring, n_buffered, nullptr, q, o, stream);
+}
+
+int sketchssm_full_read_baseline(const skssm_config* cfg, const float* S, const skssm_ring* ring,
+                                 int32_t n_buffered, const void* q, float* o, void* stream) {
+  return full_read(cfg, S, ring, n_buffered, nullptr, q, o, stream);
+}
+
+int sketchssm_step(const skssm_config* cfg, int32_t baseline, float* S, const float* omega, const float* coef,
+                   const skssm_ring* ring, int32_t n_buffered, const skssm_token* token, const void* q, void* U,
+                   void* cmap, float* o, void* stream) {
+  if (!cfg) return fail(SKSSM_EINVAL, "cfg is NULL");
+  if (!token) return fail(SKSSM_EINVAL, "token is NULL");
+  if (!q || !o) return fail(SKSSM_EINVAL, "q and o are required");
+  if (n_buffered == cfg->window - 1) {
+    if (baseline && cfg->rank != 0) return fail(SKSSM_EINVAL, "the baseline's flush needs rank 0");
+    return update(cfg, S, omega, ring, n_buffered, token, q, U, cmap, o, stream);
+  }
+  if (baseline) return full_read(cfg, S, ring, n_buffered, token, q, o, stream);
+  return decode(cfg, U, coef, cmap, S, ring, n_buffered, token, q, o, stream);
 }
 
 int sketchssm_buffer_sizes(const skssm_config* cfg, int32_t baseline, skssm_buffer_sizes* out) {

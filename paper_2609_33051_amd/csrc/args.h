@@ -6,7 +6,9 @@
 // head-major within a slot, so the four items of a decode workgroup, one head
 // and four consecutive requests, are adjacent).
 // Raw inputs of token s (k, v, beta, log decay) are written into slot s by
-// the producer of the token; the kernels derive and store the rest.
+// the producer of the token, or, where the call is given the token's own
+// arrays (tk, tv, tbeta, tla), by the kernel that reads it; the kernels derive
+// and store the rest.
 #pragma once
 
 #include <stddef.h>
@@ -36,6 +38,10 @@ struct DecodeArgs {
   void* rf;                       // ring [W][H][B][R]  projected erase factors, sketch dtype (GDN/KDA sketch read)
   float* rpi;                     // ring [W][H][B][K]  erase factors (GDN/KDA baseline)
   float* rt;                      // ring [W][H][B][W]  rows of T^{-1} (GDN/KDA)
+  const void* tk;                 // token [B][H][K] io, [B][H][V] io, [B][H], [B][H] or [B][H][K]: the current
+  const void* tv;                 // token's raw inputs, appended to slot n by this call (all NULL: the slot
+  const float* tbeta;             // already holds them)
+  const float* tla;
   float* o;                       // [B][H][V]
 };
 
@@ -55,6 +61,10 @@ struct UpdateArgs {
   void* U;                        // [B][H][R/P][V][P], P = 4 (fp32) or 8 (bf16), or NULL
   void* cmap;                     // [B][H][K/CPW][R][CPW] state-dependent map, sketch dtype, or NULL
   float ridge;                    // its lambda
+  const void* tk;                 // the current token's raw inputs, appended to slot n by this call (or all NULL)
+  const void* tv;
+  const float* tbeta;
+  const float* tla;
   float* o;                       // [B][H][V] or NULL
 };
 

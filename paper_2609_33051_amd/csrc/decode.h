@@ -15,8 +15,9 @@
 //
 // The token's raw update inputs (k, v, beta, log alpha) were written into
 // ring slot n by their producer, so appending costs no copy: the kernels read
-// them there and store only derived fields (GDN/KDA: u, f or pi, the row of
-// couplings b; KDA: the cumulative log decay).  For scalar decays the
+// them there and store only derived fields (GDN/KDA: f or pi, the row of
+// T^{-1}); or the call is given the token's own arrays, and the kernel reads
+// them there and stores them into the slot.  For scalar decays the
 // cumulative log decays are rebuilt on the fly from the ring's log alphas.
 //
 // Mapping: one wave per item; the item index is wave-uniform, so per-item
@@ -84,18 +85,24 @@ struct RowLoads {
       }
     }
     const uint32_t koff = (uint32_t)(col * KPL), voff = (uint32_t)(col * VR);
-    const size_t cur = item * W + n;                 // slot n of this item (raw fields)
+    // the current token: slot n of this item, or the token's own arrays (the
+    // row of `item` there) when this call appends it; wave-uniform selects
+    const bool own = a.tk != nullptr;
+    const size_t cur = own ? item : item * W + n;
+    const IO* kc = static_cast<const IO*>(own ? a.tk : a.rk) + cur * K;
+    const IO* vc = static_cast<const IO*>(own ? a.tv : a.rv) + cur * V;
+    const float* lc = (own ? a.tla : a.rla) + (CHAN ? cur * K : cur);
     q_raw.load_nt(static_cast<const IO*>(a.q) + item * K + koff);
-    k_raw.load_nt(static_cast<const IO*>(a.rk) + cur * K + koff);
-    v_raw.load_nt(static_cast<const IO*>(a.rv) + cur * V + voff);
-    beta_t = a.rbeta[cur];
+    k_raw.load_nt(kc + koff);
+    v_raw.load_nt(vc + voff);
+    beta_t = (own ? a.tbeta : a.rbeta)[cur];
     if constexpr (CHAN) {
       Vec<KPL> t;
-      t.load_nt(a.rla + cur * K + koff);
+      t.load_nt(lc + koff);
 #pragma unroll
       for (int m = 0; m < KPL; ++m) la[m] = t.e[m];
     } else {
-      la[0] = a.rla[cur];
+      la[0] = *lc;
     }
 #pragma unroll
     for (int m = 0; m < GD; ++m) gprev[m] = 0.f;
@@ -122,6 +129,30 @@ struct RowLoads {
         } else {
           gs[gi][0] = a.rla[si];
         }
+      }
+    }
+  }
+
+  // Append: the token's raw inputs, loaded from its own arrays, go into ring
+  // slot n.  Called once the window's log decays have arrived (the token's
+  // loads precede them, so nothing more is waited for) and before the sketch
+  // panels are requested; a token step then needs no launch of its own for the
+  // append and moves the token once.
+  __device__ __forceinline__ void append_raw(const DecodeArgs& a, size_t item, int row, int col) const {
+    if (a.tk == nullptr) return;
+    const size_t cur = item * (size_t)a.W + a.n;
+    if (row == 0) {
+      k_raw.store(const_cast<IO*>(static_cast<const IO*>(a.rk)) + cur * K + col * KPL);
+      v_raw.store(const_cast<IO*>(static_cast<const IO*>(a.rv)) + cur * V + col * VR);
+      if constexpr (CHAN) {
+        Vec<KPL> t;
+#pragma unroll
+        for (int m = 0; m < KPL; ++m) t.e[m] = la[m];
+        t.store(const_cast<float*>(a.rla) + cur * K + col * KPL);
+      }
+      if (col == 0) {
+        const_cast<float*>(a.rbeta)[cur] = beta_t;
+        if constexpr (!CHAN) const_cast<float*>(a.rla)[cur] = la[0];
       }
     }
   }
@@ -350,6 +381,7 @@ __device__ __forceinline__ void full_read_item(const DecodeArgs& a, size_t item,
   float* b_l = ob_l + V;
 
   r.prefix_decay(n, row);
+  r.append_raw(a, item, row, col);
   float qv[KPL], kv[KPL], gt[GD];
 #pragma unroll
   for (int m = 0; m < KPL; ++m) {
@@ -597,6 +629,7 @@ __global__ __launch_bounds__(256) void decode_kernel(const DecodeArgs a) {
   float* b_l = ob_l + V;
 
   r.prefix_decay(n, row);
+  r.append_raw(a, item, row, col);
   float qv[KPL], kv[KPL], gt[GD];
 #pragma unroll
   for (int m = 0; m < KPL; ++m) {

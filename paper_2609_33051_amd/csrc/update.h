@@ -569,6 +569,9 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
     // the window's current slot (then it is the last one)
     const int n = CH == 1 ? nw : !flush ? 0 : (nw - sb < SP ? nw - sb : SP - 1);
     const bool last = CH == 1 || !flush || nw < sb + SP;
+    // slot n of this chunk comes from the token's own arrays (and is appended
+    // to the ring below) when the call was given them
+    const bool own = last && a.tk != nullptr;
     float bl = 0.f, ll = 0.f;             // wave 0, lane s: beta_s and (scalar decay) log alpha_s
     float gk[CHAN ? SP : 1];              // KDA: g_s of channel tid
     Raw<IO, KPL> kr[NG / 4];              // ring keys, row layout (slot 4 (wave + 4 gq) + row)
@@ -579,14 +582,16 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
       // issued before any is used (slots past n re-read slot n, in bounds, and
       // are masked afterwards), so no load waits on a branch
       if (tid < SP) {
-        const size_t si = item * W + sb + (tid < n ? tid : n);
-        bl = a.rbeta[si];
-        if constexpr (!CHAN) ll = a.rla[si];
+        const bool tok = own && tid >= n;
+        const size_t si = tok ? item : item * W + sb + (tid < n ? tid : n);
+        bl = (tok ? a.tbeta : a.rbeta)[si];
+        if constexpr (!CHAN) ll = (tok ? a.tla : a.rla)[si];
       }
       if constexpr (CHAN) {
         if (tid < K) {
+          const float* lcur = own ? a.tla + item * K : a.rla + (item * W + sb + n) * K;
 #pragma unroll
-          for (int s = 0; s < SP; ++s) gk[s] = a.rla[(item * W + sb + (s < n ? s : n)) * K + tid];
+          for (int s = 0; s < SP; ++s) gk[s] = (s < n ? a.rla + (item * W + sb + s) * K : lcur)[tid];
         }
       }
 #pragma unroll
@@ -594,8 +599,9 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
         const int s = 4 * (wave + 4 * gq) + row;
         const size_t si = item * W + sb + s;
         if (s <= n) {
-          kr[gq].load(static_cast<const IO*>(a.rk) + si * K + col * KPL);
-          vr[gq].load(static_cast<const IO*>(a.rv) + si * V + col * VR);
+          const bool tok = own && s == n;
+          kr[gq].load((tok ? static_cast<const IO*>(a.tk) + item * K : static_cast<const IO*>(a.rk) + si * K) + col * KPL);
+          vr[gq].load((tok ? static_cast<const IO*>(a.tv) + item * V : static_cast<const IO*>(a.rv) + si * V) + col * VR);
         }
       }
       if (ch == 0) qr.load(static_cast<const IO*>(a.q) + item * K + (tid < K ? tid : K - 1));
@@ -682,6 +688,23 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
 #pragma unroll
         for (int m = 0; m < VR; m += 4)
           *reinterpret_cast<float4*>(&Us[s * UP + col * VR + m]) = make_float4(vsv[m], vsv[m + 1], vsv[m + 2], vsv[m + 3]);
+      }
+      if (own) {  // append the token to the ring
+        const size_t cur = item * W + nw;
+#pragma unroll
+        for (int gq = 0; gq < NG / 4; ++gq) {
+          if (4 * (wave + 4 * gq) + row == n) {
+            kr[gq].store(const_cast<IO*>(static_cast<const IO*>(a.rk)) + cur * K + col * KPL);
+            vr[gq].store(const_cast<IO*>(static_cast<const IO*>(a.rv)) + cur * V + col * VR);
+          }
+        }
+        if (tid == n) {
+          const_cast<float*>(a.rbeta)[cur] = bl;
+          if constexpr (!CHAN) const_cast<float*>(a.rla)[cur] = ll;
+        }
+        if constexpr (CHAN) {
+          if (tid < K) const_cast<float*>(a.rla)[cur * K + tid] = gk[SP - 1];  // every slot from n on holds log alpha_n
+        }
       }
       if (ch == 0 && tid < K) qs[tid] = qr.get(0);
       if (tid < 64) {
@@ -1026,22 +1049,27 @@ __global__ __launch_bounds__(256) void token_kernel(const UpdateArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
   const size_t item = blockIdx.x;                    // b * H + h
-  const size_t cur = item * (size_t)a.W + a.n;       // the token's raw ring slot
+  // the token's raw inputs: its ring slot, or its own arrays (then appended)
+  const bool own = a.tk != nullptr;
+  const size_t slot = item * (size_t)a.W + a.n, cur = own ? item : slot;
+  const IO* tk = static_cast<const IO*>(own ? a.tk : a.rk);
+  const IO* tv = static_cast<const IO*>(own ? a.tv : a.rv);
+  const float* tla = own ? a.tla : a.rla;
 
   // ---- the token's small loads, then the single read of the state
   float kk = 0.f, qq = 0.f, lk = 0.f;
   if (tid < K) {
-    kk = load1<IO>(static_cast<const IO*>(a.rk) + cur * K + tid);
+    kk = load1<IO>(tk + cur * K + tid);
     qq = load1<IO>(static_cast<const IO*>(a.q) + item * K + tid);
-    if constexpr (CHAN) lk = a.rla[cur * K + tid];
+    if constexpr (CHAN) lk = tla[cur * K + tid];
   }
-  const float beta = a.rbeta[cur];
-  const float ls = CHAN ? 0.f : a.rla[cur];
+  const float beta = (own ? a.tbeta : a.rbeta)[cur];
+  const float ls = CHAN ? 0.f : tla[cur];
   float vv[VTW];
 #pragma unroll
   for (int t = 0; t < VTW; ++t) {
     const int vt = wave + 4 * t;
-    vv[t] = vt < VT ? load1<IO>(static_cast<const IO*>(a.rv) + cur * V + 16 * vt + lr) : 0.f;
+    vv[t] = vt < VT ? load1<IO>(tv + cur * V + 16 * vt + lr) : 0.f;
   }
   floatx4 xs[VTW][MT];
 #pragma unroll
@@ -1061,6 +1089,20 @@ __global__ __launch_bounds__(256) void token_kernel(const UpdateArgs a) {
     ks[tid] = kk;
     qs[tid] = qq;
     if constexpr (CHAN) as[tid] = fast_exp(lk);
+  }
+  if (own) {  // append the token to the ring (io values round-trip through fp32 exactly)
+    if (tid < K) {
+      st_elem<IO>(const_cast<IO*>(static_cast<const IO*>(a.rk)) + slot * K + tid, kk);
+      if constexpr (CHAN) const_cast<float*>(a.rla)[slot * K + tid] = lk;
+    }
+#pragma unroll
+    for (int t = 0; t < VTW; ++t)
+      if (lg == 0 && wave + 4 * t < VT)
+        st_elem<IO>(const_cast<IO*>(static_cast<const IO*>(a.rv)) + slot * V + 16 * (wave + 4 * t) + lr, vv[t]);
+    if (tid == 0) {
+      const_cast<float*>(a.rbeta)[slot] = beta;
+      if constexpr (!CHAN) const_cast<float*>(a.rla)[slot] = ls;
+    }
   }
   lds_barrier();  // LDS only: the state loads stay in flight
   const float alpha = CHAN ? 1.f : fast_exp(ls);

@@ -166,6 +166,23 @@ class TestValidation:
         assert status(f, cfg(), None, good_ring(), 0, ADDR, ADDR) == -1
         assert status(f, cfg(dv=32), ADDR, good_ring(), 0, ADDR, ADDR) == -2
 
+    def test_step_rejections(self, lib):
+        """The one-launch step rejects what the call it stands for rejects, and
+        a token that is missing or misaligned."""
+        def step(c, n, baseline=False, S=ADDR, ring=None, k=ADDR, v=ADDR, beta=ADDR, la=ADDR, q=ADDR, U=ADDR, o=ADDR,
+                 coef=ADDR, cmap=None):
+            return status(lambda: B.sketchssm_step(c, baseline, S, ADDR, coef, ring or good_ring(), n, k, v, beta, la, q, U,
+                                                   o, cmap=cmap))
+        assert step(cfg(), 0, k=None) == -1 and step(cfg(), 15, la=None) == -1
+        assert step(cfg(), 0, v=ADDR + 8) == -3 and step(cfg(), 15, beta=ADDR + 4) == -3
+        assert step(cfg(), 0, q=None) == -1 and step(cfg(), 15, q=None) == -1 and step(cfg(), 15, o=None) == -1
+        assert step(cfg(), 16) == -4 and step(cfg(), -1) == -4
+        assert step(cfg(), 0, coef=None) == -1 and step(cfg(pivots=4), 0) == -1
+        assert step(cfg(), 15, S=None) == -1
+        assert step(cfg(rank=0), 16, baseline=True) == -4 and step(cfg(), 15, baseline=True) == -1
+        assert step(cfg(kind="gdn", dv=128, rank=0), 0, baseline=True, ring=good_ring(pi=None)) == -1
+        assert step(cfg(dv=32), 0) == -2 and step(cfg(dv=32), 15) == -2
+
     def test_head_rank_table(self, lib):
         """Per-head rank tables are validated on the host; calls with nothing to
         do for their path return OK without a launch."""

@@ -135,7 +135,7 @@ int launched(int rc, const char* what) {
 }
 
 // The current token's own arrays (sketchssm_step): all required, aligned like
-// every pointer; `t` NULL (the other calls) leaves the arguments NULL.
+// every pointer.
 int check_token(const skssm_token* t) {
   if (!t->k || !t->v || !t->beta || !t->log_decay) return fail(SKSSM_EINVAL, "token k/v/beta/log_decay is NULL");
   if (!aligned(t->k) || !aligned(t->v) || !aligned(t->beta) || !aligned(t->log_decay))
@@ -143,15 +143,8 @@ int check_token(const skssm_token* t) {
   return SKSSM_OK;
 }
 
-template <class A> void put_token(A& a, const skssm_token* t) {
-  if (!t) return;
-  a.tk = t->k;
-  a.tv = t->v;
-  a.tbeta = t->beta;
-  a.tla = t->log_decay;
-}
-
-skssm::DecodeArgs decode_args(const skssm_config* c, const skssm_ring* r, int32_t n, const void* q, float* o) {
+skssm::DecodeArgs decode_args(const skssm_config* c, const skssm_ring* r, int32_t n, const skssm_token* t, const void* q,
+                              float* o) {
   skssm::DecodeArgs a{};
   a.B = c->batch;
   a.H = c->heads;
@@ -165,6 +158,21 @@ skssm::DecodeArgs decode_args(const skssm_config* c, const skssm_ring* r, int32_
   a.rf = r->f;
   a.rpi = r->pi;
   a.rt = r->tinv;
+  if (t) {
+    a.ck = t->k;
+    a.cv = t->v;
+    a.cbeta = t->beta;
+    a.cla = t->log_decay;
+    a.cs = 1;
+    a.append = 1;
+  } else {  // slot n of the ring
+    const size_t io = c->io_dtype == SKSSM_BF16 ? 2 : 4;
+    a.ck = static_cast<const char*>(r->k) + (size_t)n * c->dk * io;
+    a.cv = static_cast<const char*>(r->v) + (size_t)n * c->dv * io;
+    a.cbeta = r->beta + n;
+    a.cla = r->log_decay + (size_t)n * (c->kind == SKSSM_KDA ? c->dk : 1);
+    a.cs = c->window;
+  }
   a.o = o;
   return a;
 }
@@ -217,7 +225,12 @@ int update(const skssm_config* cfg, float* S, const float* omega, const skssm_ri
     if (!aligned(q)) return fail(SKSSM_EALIGN, "q not aligned");
     if ((rc = check_ring(cfg, ring, false, false))) return rc;
     if (token && (rc = check_token(token))) return rc;
-    put_token(a, token);
+    if (token) {
+      a.tk = token->k;
+      a.tv = token->v;
+      a.tbeta = token->beta;
+      a.tla = token->log_decay;
+    }
     a.nt = n_buffered + 1;
     a.q = q;
     a.rk = ring->k;
@@ -269,8 +282,7 @@ int decode(const skssm_config* cfg, const void* U, const float* coef, const void
   }
   if ((rc = check_ring(cfg, ring, rk.sketched > 0, rk.dense > 0))) return rc;
   if (token && (rc = check_token(token))) return rc;
-  skssm::DecodeArgs a = decode_args(cfg, ring, n_buffered, q, o);
-  put_token(a, token);
+  skssm::DecodeArgs a = decode_args(cfg, ring, n_buffered, token, q, o);
   put_ranks(a, rk);
   put_order(a, rk);
   a.S = rk.dense ? S : nullptr;
@@ -299,8 +311,7 @@ int full_read(const skssm_config* cfg, const float* S, const skssm_ring* ring, i
   if (!aligned(S) || !aligned(o) || !aligned(q)) return fail(SKSSM_EALIGN, "S/q/o not aligned");
   if ((rc = check_ring(cfg, ring, false, true))) return rc;
   if (token && (rc = check_token(token))) return rc;
-  skssm::DecodeArgs a = decode_args(cfg, ring, n_buffered, q, o);
-  put_token(a, token);
+  skssm::DecodeArgs a = decode_args(cfg, ring, n_buffered, token, q, o);
   a.S = S;
   int r;
   switch (cfg->kind) {

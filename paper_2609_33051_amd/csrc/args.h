@@ -38,10 +38,15 @@ struct DecodeArgs {
   void* rf;                       // ring [W][H][B][R]  projected erase factors, sketch dtype (GDN/KDA sketch read)
   float* rpi;                     // ring [W][H][B][K]  erase factors (GDN/KDA baseline)
   float* rt;                      // ring [W][H][B][W]  rows of T^{-1} (GDN/KDA)
-  const void* tk;                 // token [B][H][K] io, [B][H][V] io, [B][H], [B][H] or [B][H][K]: the current
-  const void* tv;                 // token's raw inputs, appended to slot n by this call (all NULL: the slot
-  const float* tbeta;             // already holds them)
-  const float* tla;
+  // the current token's raw inputs: row i * cs of these is item i's (ring slot
+  // n: offset to it, cs = W; or the token's own arrays [B][H][..], cs = 1,
+  // which this call appends to the slot)
+  const void* ck;                 // rows of K io
+  const void* cv;                 // rows of V io
+  const float* cbeta;             // rows of 1
+  const float* cla;               // rows of 1 or K
+  int cs;
+  int append;                     // the token comes from its own arrays
   float* o;                       // [B][H][V]
 };
 

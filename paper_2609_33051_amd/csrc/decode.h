@@ -85,24 +85,18 @@ struct RowLoads {
       }
     }
     const uint32_t koff = (uint32_t)(col * KPL), voff = (uint32_t)(col * VR);
-    // the current token: slot n of this item, or the token's own arrays (the
-    // row of `item` there) when this call appends it; wave-uniform selects
-    const bool own = a.tk != nullptr;
-    const size_t cur = own ? item : item * W + n;
-    const IO* kc = static_cast<const IO*>(own ? a.tk : a.rk) + cur * K;
-    const IO* vc = static_cast<const IO*>(own ? a.tv : a.rv) + cur * V;
-    const float* lc = (own ? a.tla : a.rla) + (CHAN ? cur * K : cur);
+    const size_t cur = item * (size_t)a.cs;          // the current token's row
     q_raw.load_nt(static_cast<const IO*>(a.q) + item * K + koff);
-    k_raw.load_nt(kc + koff);
-    v_raw.load_nt(vc + voff);
-    beta_t = (own ? a.tbeta : a.rbeta)[cur];
+    k_raw.load_nt(static_cast<const IO*>(a.ck) + cur * K + koff);
+    v_raw.load_nt(static_cast<const IO*>(a.cv) + cur * V + voff);
+    beta_t = a.cbeta[cur];
     if constexpr (CHAN) {
       Vec<KPL> t;
-      t.load_nt(lc + koff);
+      t.load_nt(a.cla + cur * K + koff);
 #pragma unroll
       for (int m = 0; m < KPL; ++m) la[m] = t.e[m];
     } else {
-      la[0] = *lc;
+      la[0] = a.cla[cur];
     }
 #pragma unroll
     for (int m = 0; m < GD; ++m) gprev[m] = 0.f;
@@ -137,9 +131,10 @@ struct RowLoads {
   // slot n.  Called once the window's log decays have arrived (the token's
   // loads precede them, so nothing more is waited for) and before the sketch
   // panels are requested; a token step then needs no launch of its own for the
-  // append and moves the token once.
+  // append and moves the token once.  A kernel of its own (APPEND): a run-time
+  // branch around these stores cost the plain read 0.5 % (KDA, B = 512: 52.6 ->
+  // 52.85 us a read), as loads in flight across its join are waited for early.
   __device__ __forceinline__ void append_raw(const DecodeArgs& a, size_t item, int row, int col) const {
-    if (a.tk == nullptr) return;
     const size_t cur = item * (size_t)a.W + a.n;
     if (row == 0) {
       k_raw.store(const_cast<IO*>(static_cast<const IO*>(a.rk)) + cur * K + col * KPL);
@@ -347,7 +342,7 @@ __device__ __forceinline__ void append_derived(const DecodeArgs& a, size_t dp, i
 // (eq. app-effective-query-wy), storing pi_t and row n of T^{-1} for the
 // token.  dp: the item's position in the derived ring fields (h * B + b).
 // ws: the wave's 2V + 2 WMAX + K floats of LDS.
-template <int KIND, int K, int V, int WMAX, typename IO>
+template <int KIND, int K, int V, int WMAX, typename IO, bool APPEND>
 __device__ __forceinline__ void full_read_item(const DecodeArgs& a, size_t item, size_t dp, int lane, float* ws) {
   using L = RowLoads<KIND, K, V, WMAX, IO>;
   constexpr bool ERASE = L::ERASE, CHAN = L::CHAN;
@@ -381,7 +376,7 @@ __device__ __forceinline__ void full_read_item(const DecodeArgs& a, size_t item,
   float* b_l = ob_l + V;
 
   r.prefix_decay(n, row);
-  r.append_raw(a, item, row, col);
+  if constexpr (APPEND) r.append_raw(a, item, row, col);
   float qv[KPL], kv[KPL], gt[GD];
 #pragma unroll
   for (int m = 0; m < KPL; ++m) {
@@ -511,9 +506,10 @@ __device__ __forceinline__ void load_map_rows(const DecodeArgs& a, size_t item, 
   }
 }
 
-// DENSE: compiled with the exact read for dense-fallback heads (launched only
+// APPEND: the current token comes from its own arrays and is stored into its
+// ring slot.  DENSE: compiled with the exact read for dense-fallback heads (launched only
 // for rank tables that have some); without it the kernel needs fewer registers.
-template <int KIND, int K, int V, int R, int WMAX, typename IO, typename SK, int P, bool DENSE>
+template <int KIND, int K, int V, int R, int WMAX, typename IO, typename SK, int P, bool DENSE, bool APPEND>
 __global__ __launch_bounds__(256) void decode_kernel(const DecodeArgs a) {
   using L = RowLoads<KIND, K, V, WMAX, IO>;
   constexpr bool ERASE = L::ERASE, CHAN = L::CHAN;
@@ -563,7 +559,7 @@ __global__ __launch_bounds__(256) void decode_kernel(const DecodeArgs a) {
     // barrier is skipped)
     static_assert(WS >= 2 * V + 2 * WMAX + K, "per-wave LDS too small for the full read");
     if constexpr (DENSE) {
-      if (valid) full_read_item<KIND, K, V, WMAX, IO>(a, item, dp, lane, wscr + wave * WS);
+      if (valid) full_read_item<KIND, K, V, WMAX, IO, APPEND>(a, item, dp, lane, wscr + wave * WS);
     }
     return;
   }
@@ -629,7 +625,7 @@ __global__ __launch_bounds__(256) void decode_kernel(const DecodeArgs a) {
   float* b_l = ob_l + V;
 
   r.prefix_decay(n, row);
-  r.append_raw(a, item, row, col);
+  if constexpr (APPEND) r.append_raw(a, item, row, col);
   float qv[KPL], kv[KPL], gt[GD];
 #pragma unroll
   for (int m = 0; m < KPL; ++m) {
@@ -788,7 +784,7 @@ __global__ __launch_bounds__(256) void decode_kernel(const DecodeArgs a) {
   }
 }
 
-template <int KIND, int K, int V, int WMAX, typename IO>
+template <int KIND, int K, int V, int WMAX, typename IO, bool APPEND>
 __global__ __launch_bounds__(256) void full_read_kernel(const DecodeArgs a) {
   constexpr int WS = 2 * V + 2 * WMAX + K;  // per-wave LDS: o^state, o_buf, alpha/gamma transposition, q~
   __shared__ __align__(16) float wscr[4 * WS];
@@ -802,7 +798,7 @@ __global__ __launch_bounds__(256) void full_read_kernel(const DecodeArgs a) {
   const size_t item = (size_t)lwg * 4 + wave;
   if (item >= NI) return;  // wave-uniform; no block barrier in this kernel
   const uint32_t b = (uint32_t)item / (uint32_t)a.H, h = (uint32_t)item - b * (uint32_t)a.H;  // B*H <= 2^30
-  full_read_item<KIND, K, V, WMAX, IO>(a, item, (size_t)h * a.B + b, lane, wscr + wave * WS);
+  full_read_item<KIND, K, V, WMAX, IO, APPEND>(a, item, (size_t)h * a.B + b, lane, wscr + wave * WS);
 }
 
 }  // namespace skssm

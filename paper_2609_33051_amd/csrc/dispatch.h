@@ -30,38 +30,61 @@ size_t lds_for_cap(Kernel kern, int cap) {
 
 // Resident workgroups per CU for the kernels that read each item's state and
 // write it back in place (the flush with the offline map or none, and the
-// single-token update).  With more of these streams resident per CU the
-// in-place stream measured slower: the flush took 431 / 456 us (Mamba-2 at six
-// per CU, GDN at four; B = 256 / 512) against 387 / 435 us at three, and the
-// Mamba-2 single-token update 391 us at eight against 342 us at two.  The
-// flushes that build a state-dependent map and the decode do arithmetic or
+// single-token update; 0: what registers and LDS allow).  With more of these
+// streams in flight per CU the in-place stream runs slower; with too few, each
+// workgroup's own latency shows.  The line lies by the bytes of an item's state
+// (4 K V) and the work between its load and store, measured at 1 GiB of state
+// (us at a cap of two / three / four / five / none):
+//   Mamba-2  16 KB  582 / 461 / 429 / 425 / 443     -> 5
+//            32 KB  433 / 397 / 422 / 438 / 444     -> 3
+//            64 KB  425 / 459 / 465 / 475 / 471     -> 2
+//   GDN      16 KB  672 / 559 / 497 / 470 / 450     -> none
+//            32 KB  575 / 489 / 440 / - / 436       -> none
+//            64 KB  456 / 432 / - / - / 421..452    -> 3  (KDA 470 / 446 / - / - / 477)
+// The flushes that build a state-dependent map and the decode do arithmetic or
 // wait on latency between their loads and keep their occupancy (capping them
 // measured slower), as does the initial sketch (a read of the state, run once
 // after prefill).
-constexpr int kFlushPerCU = 3;
+constexpr int flush_cap(int kind, int K, int V) {
+  const int kb = 4 * K * V / 1024;
+  if (kind != MAMBA2) return kb >= 64 ? 3 : 0;
+  return kb >= 64 ? 2 : kb >= 32 ? 3 : 5;
+}
 constexpr int kTokenPerCU = 2;
+
+template <int KIND, int K, int V, int R, int WM, typename IO, typename SK, int P, bool APPEND>
+int launch_decode_as(const DecodeArgs& a, hipStream_t s) {
+  const unsigned tiles = (unsigned)((a.B + 3) / 4);
+  if (a.ndense > 0)
+    hipLaunchKernelGGL((decode_kernel<KIND, K, V, R, WM, IO, SK, P, true, APPEND>), dim3((unsigned)a.H * tiles), dim3(256), 0,
+                       s, a);
+  else
+    hipLaunchKernelGGL((decode_kernel<KIND, K, V, R, WM, IO, SK, P, false, APPEND>), dim3((unsigned)a.H * tiles), dim3(256), 0,
+                       s, a);
+  return 0;
+}
 
 template <int KIND, int K, int V, int R, int WM, typename IO, typename SK, int P>
 int launch_decode(const DecodeArgs& a, hipStream_t s) {
-  const unsigned tiles = (unsigned)((a.B + 3) / 4);
-  if (a.ndense > 0)
-    hipLaunchKernelGGL((decode_kernel<KIND, K, V, R, WM, IO, SK, P, true>), dim3((unsigned)a.H * tiles), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL((decode_kernel<KIND, K, V, R, WM, IO, SK, P, false>), dim3((unsigned)a.H * tiles), dim3(256), 0, s, a);
-  return 0;
+  return a.append ? launch_decode_as<KIND, K, V, R, WM, IO, SK, P, true>(a, s)
+                  : launch_decode_as<KIND, K, V, R, WM, IO, SK, P, false>(a, s);
 }
 
 template <int KIND, int K, int V, int WM, typename IO>
 int launch_full_read(const DecodeArgs& a, hipStream_t s) {
-  const size_t items = (size_t)a.B * a.H;
-  hipLaunchKernelGGL((full_read_kernel<KIND, K, V, WM, IO>), dim3((unsigned)((items + 3) / 4)), dim3(256), 0, s, a);
+  const unsigned groups = (unsigned)(((size_t)a.B * a.H + 3) / 4);
+  if (a.append)
+    hipLaunchKernelGGL((full_read_kernel<KIND, K, V, WM, IO, true>), dim3(groups), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL((full_read_kernel<KIND, K, V, WM, IO, false>), dim3(groups), dim3(256), 0, s, a);
   return 0;
 }
 
 template <int KIND, int K, int V, int R, int WM, typename IO, typename SK, int P>
 int launch_update(const UpdateArgs& a, hipStream_t s) {
   const size_t items = (size_t)a.B * a.H;
-  static const size_t cap = P == 0 ? lds_for_cap(&update_kernel<KIND, K, V, R, WM, IO, SK, P>, kFlushPerCU) : 0;
+  constexpr int kCap = P == 0 ? flush_cap(KIND, K, V) : 0;
+  static const size_t cap = kCap ? lds_for_cap(&update_kernel<KIND, K, V, R, WM, IO, SK, P>, kCap) : 0;
   hipLaunchKernelGGL((update_kernel<KIND, K, V, R, WM, IO, SK, P>), dim3((unsigned)items), dim3(256), a.nt > 0 ? cap : 0,
                      s, a);
   return 0;

@@ -19,7 +19,9 @@
 //
 // Mapping: one workgroup (4 waves) per (request, head) item.  The window's
 // slots are staged into LDS with wide loads (row layout: four slots per load
-// instruction, wave w taking slot groups w, w + 4, ...).  Each wave owns
+// instruction, wave w taking slot groups w, w + 4, ...), the keys transposed so
+// that a matrix-core operand over slots (or, for -Pi and Omega^T, over
+// channels) is one 16-byte LDS read.  Each wave owns
 // 16-column value tiles of X^T (K rows x 16 values), held in MFMA
 // accumulator layout: lane l holds X[v0 + l%16][16 kt + 4 (l/16) + i],
 // i = 0..3.  The state is stored in exactly this order (tile-major: tile
@@ -67,7 +69,7 @@ template <> __device__ __forceinline__ float load1<bf16_t>(const bf16_t* p) { re
 // sketch's dtype (bf16 with the paper's storage, rounded to nearest even) in
 // 16-byte channel panels cmap[B][H][K/CPW][G][CPW].  Rows past the head's
 // rank are not stored.  Every thread of the workgroup calls this.
-template <int K, int R, int P, int MT, int RT, int LSZ, int USZ, int OPJ, typename SK>
+template <int K, int R, int P, int MT, int RT, int LSZ, int USZ, int OPK, typename SK>
 __device__ __forceinline__ void coef_map_tail(const UpdateArgs& a, size_t item, int wave, int lane, int tid, int rh,
                                               const floatx4 (&nacc)[MT], const floatx4 (&gram)[RT],
                                               const float (&dsq)[RT], float msq,
@@ -250,11 +252,9 @@ __device__ __forceinline__ void coef_map_tail(const UpdateArgs& a, size_t item, 
     }
 #pragma unroll
     for (int h4 = 0; h4 < R; h4 += 4) {
-      const float4 o4 = *reinterpret_cast<const float4*>(&OmL[k * OPJ + h4]);
-      const float oh[4] = {o4.x, o4.y, o4.z, o4.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float wo = sL[R * P + h4 + e] * oh[e];
+        const float wo = sL[R * P + h4 + e] * OmL[(h4 + e) * OPK + k];
 #pragma unroll
         for (int x = 0; x < P; ++x) Mk[x] -= sL[(h4 + e) * P + x] * wo;
       }
@@ -283,8 +283,11 @@ __device__ __forceinline__ void coef_map_tail(const UpdateArgs& a, size_t item, 
       floatx4 acc = {0.f, 0.f, 0.f, 0.f};
       acc = mfma4(Mb[(16 * kt + lr) * P + lg], Fb[(16 * jt + lr) * FBP + lg], acc);
       const float wj = j < R ? sL[R * P + j] : 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] += wj * OmL[(k0 + i) * OPJ + j];
+      const float4 o4 = *reinterpret_cast<const float4*>(&OmL[j * OPK + k0]);
+      acc[0] += wj * o4.x;
+      acc[1] += wj * o4.y;
+      acc[2] += wj * o4.z;
+      acc[3] += wj * o4.w;
       if (j < rh) st_elem4<SK>(cm + ((size_t)(k0 / CPW) * R + j) * CPW + k0 % CPW, acc[0], acc[1], acc[2], acc[3]);
     }
   }
@@ -401,56 +404,103 @@ __device__ __forceinline__ void coef_map_exact_tail(const UpdateArgs& a, size_t 
   }
 }
 
-// The rank update of one 16-value tile of X = S^T from the factors of a window
-// (or a chunk of one) staged in LDS, eq. wy: lane (lr, lg) holds
-// X[v][16 kt + 4 lg + i] in x[kt][i], v = 16 vt + lr, and
+// LDS layout of a [K][S] array of per-channel slot vectors (keys or left
+// factors, transposed): channel ch starts at slot_row<S>(ch), its S slots
+// contiguous, so an operand over slots is one 16-byte read.  Rows are S + 4
+// words apart (the operand reads of 16 consecutive channels hit all banks) and
+// every eighth row is shifted by 4 more (as do the staging writes, whose lanes
+// are 8 channels apart).
+template <int S> __device__ __forceinline__ int slot_row(int ch) { return ch * (S + 4) + (ch >> 3) * 4; }
+
+__device__ __forceinline__ floatx4 lds4(const float* p) {
+  const float4 t = *reinterpret_cast<const float4*>(p);
+  return floatx4{t.x, t.y, t.z, t.w};
+}
+
+// The rank update of a wave's 16-value tiles of X = S^T from the factors of a
+// window (or a chunk of one) in LDS, eq. wy: lane (lr, lg) holds
+// X[v][16 kt + 4 lg + i] of tile t in x[t][kt][i], v = 16 (wave + 4 t) + lr, and
 //   X^T <- Diag(e^{g_n}) X^T + (keys or L)^T W^T,
 // with w_s = c_s (u_s - (Pi X^T)[s]) (GDN), u_s - (Pi X^T)[s] (KDA, whose decays
-// are in L and ds) or c_s beta_s v_s (Mamba-2), slot s = 16 st + 4 lg + i.
-template <int KIND, int MT, int ST, int LP, int PP, int UP>
-__device__ __forceinline__ void rank_update_tile(floatx4 (&x)[MT], int v, int lr, int lg, float egn, const float* Ls,
-                                                 const float* PiT, const float* Us, const float* bsl, const float* csc,
-                                                 const float* ds) {
+// are in L and ds) or c_s beta_s v_s (Mamba-2), slot s = 16 st + 4 lg + i.  For
+// the erase families u = T^{-1} (beta . v) is formed here too: tu holds this
+// lane's entries of T^{-1} Diag(beta) (row lr, columns 4 lg ..), Vs the raw
+// values, and nPi is -Pi.  Every operand read serves all of the wave's tiles.
+template <int KIND, int MT, int ST, int VTW, int LP, int UP, int NC>
+__device__ __forceinline__ void rank_update(floatx4 (&x)[VTW][MT], int wave, int lr, int lg, float egn, const float* LT,
+                                            const float* nPi, const float* Vs, const floatx4& tu, const float* bsl,
+                                            const float* csc, const float* ds) {
   constexpr bool ERASE = KIND != MAMBA2;
   constexpr bool CHAN = KIND == KDA;
-  floatx4 wv[ST];
+  floatx4 wv[VTW][ST];
+  if constexpr (ERASE) {
+    static_assert(ST == 1, "an erase family's chunk has 16 slots");
+    // -(Pi X^T)[s] in NC accumulation chains per tile, u apart from them: u is
+    // the larger term, and sums started from it round to its size (state error
+    // against 64 bits 2.2e-7, with this order 1.0e-7)
+    floatx4 pc[VTW][NC];
 #pragma unroll
-  for (int st = 0; st < ST; ++st) {
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (ERASE) {
-      // (Pi X^T)[s] in four independent accumulation chains
-      floatx4 pc[4];
+    for (int t = 0; t < VTW; ++t)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) pc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (int c = 0; c < NC; ++c) pc[t][c] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kt = 0; kt < MT; ++kt)
+    for (int kt = 0; kt < MT; ++kt) {
+      const floatx4 a = lds4(&nPi[lr * LP + 16 * kt + 4 * lg]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          pc[i] = mfma4(PiT[(16 * kt + 4 * lg + i) * PP + 16 * st + lr], x[kt][i], pc[i]);
-      acc = (pc[0] + pc[1]) + (pc[2] + pc[3]);
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int t = 0; t < VTW; ++t) pc[t][i % NC] = mfma4(a[i], x[t][kt][i], pc[t][i % NC]);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int s = 16 * st + 4 * lg + i;
-      float w = Us[s * UP + v] - acc[i];
-      if constexpr (!ERASE) w *= bsl[s] * csc[s];
-      if constexpr (ERASE && !CHAN) w *= csc[s];
-      wv[st][i] = w;
+    for (int t = 0; t < VTW; ++t) {
+      floatx4 u = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) u = mfma4(tu[i], Vs[(4 * lg + i) * UP + 16 * (wave + 4 * t) + lr], u);
+      wv[t][0] = pc[t][0] + pc[t][1];
+      if constexpr (NC == 4) wv[t][0] += pc[t][2] + pc[t][3];
+      wv[t][0] += u;
+      if constexpr (!CHAN) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) wv[t][0][i] *= csc[4 * lg + i];
+      }
     }
-  }
-#pragma unroll
-  for (int kt = 0; kt < MT; ++kt) {
-    floatx4 acc;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] = x[kt][i] * (CHAN ? ds[16 * kt + 4 * lg + i] : egn);
+  } else {
 #pragma unroll
     for (int st = 0; st < ST; ++st)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc = mfma4(Ls[(16 * st + 4 * lg + i) * LP + 16 * kt + lr], wv[st][i], acc);
-    x[kt] = acc;
+      for (int i = 0; i < 4; ++i) {
+        const int s = 16 * st + 4 * lg + i;
+        const float f = bsl[s] * csc[s];
+#pragma unroll
+        for (int t = 0; t < VTW; ++t) wv[t][st][i] = Vs[s * UP + 16 * (wave + 4 * t) + lr] * f;
+      }
+  }
+#pragma unroll
+  for (int kt = 0; kt < MT; ++kt) {
+    floatx4 d = {egn, egn, egn, egn};
+    if constexpr (CHAN) d = lds4(&ds[16 * kt + 4 * lg]);
+#pragma unroll
+    for (int t = 0; t < VTW; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[t][kt][i] *= d[i];
+#pragma unroll
+    for (int st = 0; st < ST; ++st) {
+      const floatx4 a = lds4(&LT[slot_row<16 * ST>(16 * kt + lr) + 16 * st + 4 * lg]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int t = 0; t < VTW; ++t) x[t][kt] = mfma4(a[i], wv[t][st][i], x[t][kt]);
+    }
   }
 }
 
+// What bounds it: the in-place stream of the state (8 K V bytes an item).  A GDN
+// item (K = V = 128, W = 16) alone on a CU takes 8.7 us from launch to end, 2.6
+// of them fp32 matrix-core time; before the channel work went to the matrix
+// cores it took 12.9, and B = 512 flushes (2.5 GB) went from 452 to 427 us (GDN)
+// and from 476 to 445 (KDA), the two-chunk W = 32 flush at B = 256 from 335 to
+// 266, and those with a P = 4 map from 517 to 472 (GDN) and 591 to 509 (KDA).
+//
 // Three workgroups per CU, or four for the state-dependent maps (P = 4 and
 // exact) at window 16 and rank <= 16: their flush spends part of each
 // workgroup's life off the memory bus (the map's products and algebra), so
@@ -474,22 +524,28 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
   constexpr int ST = SP / 16;         // slot tiles
   constexpr int NG = SP / 4;          // slot groups of four
   constexpr int RT = (R + 15) / 16;   // sketch tiles
+  // accumulation chains per tile of X_0 Pi^T and of the sketch: more chains
+  // shorten the dependent sums (and round less), two tiles' worth of four spill
+  // where the map's bound leaves 128 registers (KDA, P = 4: 132 bytes per lane)
+  constexpr int NCW = P == 0 || VTW == 1 ? 4 : 2;
+  constexpr int NCU = P == 0 || VTW == 1 ? 2 : 1;
   constexpr int KPL = K / 16;         // key channels per lane (row layout)
   constexpr int VR = V / 16;          // value channels per lane (row layout)
   constexpr int LP = K + 4;           // LDS pitches chosen so that the 4 lane
-  constexpr int PP = SP + 4;          // groups of an operand read land in
-  constexpr int UP = V + 4;           // different banks
-  constexpr int KW = (K + 63) / 64;   // waves that carry channel work
+  constexpr int UP = V + 4;           // groups of an operand read land in different banks
+  constexpr int LSZ = K * (SP + 4) + K / 2;  // words of a slot_row array
 
-  __shared__ __align__(16) float Ls[SP * LP];                 // keys k_s (KDA: then L[s]), [s][k]
-  __shared__ __align__(16) float PiT[ERASE ? K * PP : 4];     // Pi^T[k][s]
-  __shared__ __align__(16) float Us[SP * UP];                 // raw v_s (Mamba-2) or u_s
-  __shared__ float Bs[ERASE ? SP * SP : 1];                   // (T^{-1})_{s,j}, j < s < n
-  __shared__ float bpart[ERASE ? KW * SP : 1];                // partial sums of b_{n,j}
+  __shared__ __align__(16) float Ls[LSZ];                     // keys k_s (KDA: then L[s]), transposed (slot_row)
+  // -Pi, [s][k]; for KDA first e^{g_s} . k_s, transposed (slot_row)
+  __shared__ __align__(16) float Pi[!ERASE ? 4 : CHAN && LSZ > SP * LP ? LSZ : SP * LP];
+  __shared__ __align__(16) float Us[SP * UP];                 // raw v_s, [s][v]
+  __shared__ __align__(16) float Bs[ERASE ? SP * SP : 4];     // (T^{-1})_{s,j}, j < s < n
+  __shared__ float dl[ERASE ? SP : 4];                        // <k_s, k_n> (KDA: <L[s], k_n> = b_{n,s})
   __shared__ __align__(16) float qs[K];
   __shared__ __align__(16) float ds[CHAN ? K : 4];            // e^{g_n} per channel (KDA)
-  __shared__ float csc[SP];                                   // c_s = e^{g_n - g_s} (scalar decay)
-  __shared__ float bsl[SP], gsl[SP];                          // beta_s, g_s (0 past slot n)
+  __shared__ __align__(16) float csc[SP];                     // c_s = e^{g_n - g_s} (scalar decay), 0 past slot n
+  __shared__ __align__(16) float bsl[SP], bel[SP];            // beta_s, beta_s e^{g_s} (0 past slot n)
+  __shared__ float egl[4];                                    // e^{g_n} (scalar decay)
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -503,13 +559,14 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
   // fields at (s * B*H + dp) * width, dp = h * B + b
   const size_t NI = (size_t)a.B * H, dp = (size_t)h * a.B + blockIdx.x / (uint32_t)H;
 
-  // Omega of this head goes to LDS (rows padded to whole 16-column tiles plus
-  // four words, so the four lane groups of an operand read hit different banks)
-  // when it is small; the full-rank case reads it from global memory.
+  // Omega^T of this head goes to LDS (one row per sketch column, rows padded so
+  // that the 16 columns of an operand read hit different banks; columns padded
+  // with zeros to whole 16-column tiles) when it is small; the full-rank case
+  // reads it from global memory.
   constexpr bool OM_LDS = R > 0 && R <= 32;
-  constexpr int OPJ = 16 * RT + 4;
+  constexpr int OPK = K + 4;
   constexpr int OQ = OM_LDS ? (K * R / 4 + 255) / 256 : 1;  // float4 of Omega per thread
-  __shared__ __align__(16) float OmL[OM_LDS ? K * OPJ : 4];
+  __shared__ __align__(16) float OmL[OM_LDS ? 16 * RT * OPK : 4];
   // this head's rank (per-head rank table): the sketch uses Omega's first rh
   // columns (the rest are zeroed in LDS, so U's columns past rh come out 0 and
   // the state-dependent map's rows past rh too); rh = 0: a dense-fallback head
@@ -528,15 +585,15 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
   // keeps the kernel's LDS that of the offline-map flush (four workgroups per CU).
   // Each tile's sketch columns go through the same per-wave block as X's
   // (one after the other).
-  constexpr bool CM_ALIAS = P != 0 && SP * LP >= 4 * 16 * XP;
+  constexpr bool CM_ALIAS = P != 0 && LSZ >= 4 * 16 * XP;
   __shared__ __align__(16) float cmXs[P != 0 && !CM_ALIAS ? 4 * 16 * XP : 4];
   float* const cmX = CM_ALIAS ? Ls : cmXs;                 // [wave][16 values][16 keys]
   float* const cmU = cmX;                                  // [wave][16 values][16 sketch columns], before X's blocks
   __shared__ __align__(16) float cmS[P != 0 ? 8 + 16 + 5 * R : 4];  // mu parts, R^{-1}/sqrt(mu), L_G and w
   // F1 of the map, in its own LDS only where the key staging has no room
-  constexpr bool CMF_OWN = P > 0 && SP * LP < P * K + 16 * RT * (P + 1);
+  constexpr bool CMF_OWN = P > 0 && LSZ < P * K + 16 * RT * (P + 1);
   __shared__ __align__(16) float cmF[CMF_OWN ? 16 * RT * (P + 1) : 4];
-  static_assert(!EXACT || (SP * LP >= R * (K + 4) && SP * UP >= 2 * R * (R + 1)),
+  static_assert(!EXACT || (LSZ >= R * (K + 4) && SP * UP >= 2 * R * (R + 1)),
                 "the exact map's sums must fit the window staging");
   floatx4 nacc[P != 0 ? MT : 1];   // N^T (rows 4 lg + i: pivots a < 4, or every sketch column), this wave's values
   floatx4 gram[P > 0 ? RT : 1];    // sketch Gram U^T U_p: lane (lr, lg), i: row 16 jt + 4 lg + i, column lr < P; this wave's values
@@ -557,11 +614,36 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
 
   // ---- every small load first (window, query, rows of T^{-1}, Omega), then the
   // state: the staged values reach LDS while the state read is still in flight
-  float egn = 1.f, gn = 0.f, bn = 0.f;  // the chunk's e^{g_n} (scalar decay), g_n, beta_n (from LDS after the staging)
+  float egn = 1.f;  // the chunk's e^{g_n} (scalar decay)
+  floatx4 tu = {0.f, 0.f, 0.f, 0.f};  // this lane's entries of T^{-1} Diag(beta): row lr, columns 4 lg .. (erase families)
   Raw<IO, 1> qr;  // this thread's query channel, raw (converted at the staging, so no wait here)
   constexpr int BQ = ERASE ? (SP * SP + 255) / 256 : 1;
   Vec<4> omv[OQ];
   floatx4 xs[VTW][MT];
+  // ---- the single read of the state.  The offline-map flushes of the erase
+  // families issue it once the window is staged (its latency then overlaps the
+  // channel work): at B = 512, K = V = 128 the in-place stream runs faster the
+  // shorter a workgroup's 64 KB are in flight (three workgroups per CU, issued
+  // with the staging's loads: GDN 452 us, KDA 470; after the staging: 427, 443;
+  // after the channel work: 436, 462).  The others issue it with the staging's
+  // loads, unconditionally, so that waiting for the staged values never waits
+  // for it: Mamba-2's 32 KB (397 us either way), windows of two chunks (284
+  // against 295) and the flushes that build a map, which are not bound by the
+  // stream (GDN 492 against 507).
+  constexpr bool STATE_LATE = ERASE && CH == 1 && P == 0;
+  static_assert(VT % 4 == 0, "every wave owns the same number of value tiles");
+  auto load_state = [&]() {
+#pragma unroll
+    for (int t = 0; t < VTW; ++t) {
+      // tile (vt, kt) of the state is 1 KB contiguous, lane l's float4 at 4 l
+      const float* src = a.S + item * V * K + (size_t)((wave + 4 * t) * MT) * 256 + 4 * lane;
+#pragma unroll
+      for (int kt = 0; kt < MT; ++kt) {
+        const float4 x = ld_nt(reinterpret_cast<const float4*>(src + 256 * kt));
+        xs[t][kt] = floatx4{x.x, x.y, x.z, x.w};
+      }
+    }
+  };
 #pragma unroll
   for (int ch = 0; ch < CH; ++ch) {
     const int sb = 16 * ch;                                 // the chunk's first slot in the ring
@@ -573,9 +655,10 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
     // to the ring below) when the call was given them
     const bool own = last && a.tk != nullptr;
     float bl = 0.f, ll = 0.f;             // wave 0, lane s: beta_s and (scalar decay) log alpha_s
-    float gk[CHAN ? SP : 1];              // KDA: g_s of channel tid
+    float gk[CHAN ? SP : 1];              // KDA: g_s of channel tid % K
     Raw<IO, KPL> kr[NG / 4];              // ring keys, row layout (slot 4 (wave + 4 gq) + row)
     Raw<IO, VR> vr[NG / 4];               // raw values
+    [[maybe_unused]] Raw<IO, KPL> knr;    // GDN: the key of slot n (same in every row)
     float bv[BQ];
     if (flush) {
       // per-slot scalars: lane s of wave 0 loads slot s; every slot load is
@@ -588,11 +671,9 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
         if constexpr (!CHAN) ll = (tok ? a.tla : a.rla)[si];
       }
       if constexpr (CHAN) {
-        if (tid < K) {
-          const float* lcur = own ? a.tla + item * K : a.rla + (item * W + sb + n) * K;
+        const float* lcur = own ? a.tla + item * K : a.rla + (item * W + sb + n) * K;
 #pragma unroll
-          for (int s = 0; s < SP; ++s) gk[s] = (s < n ? a.rla + (item * W + sb + s) * K : lcur)[tid];
-        }
+        for (int s = 0; s < SP; ++s) gk[s] = (s < n ? a.rla + (item * W + sb + s) * K : lcur)[tid % K];
       }
 #pragma unroll
       for (int gq = 0; gq < NG / 4; ++gq) {
@@ -604,6 +685,9 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
           vr[gq].load((tok ? static_cast<const IO*>(a.tv) + item * V : static_cast<const IO*>(a.rv) + si * V) + col * VR);
         }
       }
+      if constexpr (ERASE && !CHAN)
+        knr.load((own ? static_cast<const IO*>(a.tk) + item * K : static_cast<const IO*>(a.rk) + (item * W + sb + n) * K) +
+                 col * KPL);
       if (ch == 0) qr.load(static_cast<const IO*>(a.q) + item * K + (tid < K ? tid : K - 1));
       if constexpr (ERASE) {
 #pragma unroll
@@ -626,23 +710,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
       }
     }
 
-    // ---- the single read of the state (unconditional where every wave owns
-    // VTW tiles, so that waiting for the staged loads never waits for these)
-    if (ch == 0) {
-#pragma unroll
-      for (int t = 0; t < VTW; ++t) {
-        const int vt = wave + 4 * t;
-        if (VT % 4 == 0 || vt < VT) {
-          // tile (vt, kt) of the state is 1 KB contiguous, lane l's float4 at 4 l
-          const float* src = a.S + item * V * K + (size_t)(vt * MT) * 256 + 4 * lane;
-#pragma unroll
-          for (int kt = 0; kt < MT; ++kt) {
-            const float4 x = ld_nt(reinterpret_cast<const float4*>(src + 256 * kt));
-            xs[t][kt] = floatx4{x.x, x.y, x.z, x.w};
-          }
-        }
-      }
-    }
+    if (!STATE_LATE && ch == 0) load_state();
     compiler_fence();
 
     // ---- staged values into LDS
@@ -656,13 +724,13 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
 #pragma unroll
             for (int e = 0; e < 4; ++e)
               if (4 * (i % (R / 4)) + e >= rh) w.e[e] = 0.f;
-            w.store(&OmL[(i / (R / 4)) * OPJ + 4 * (i % (R / 4))]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) OmL[(4 * (i % (R / 4)) + e) * OPK + i / (R / 4)] = w.e[e];
           }
         }
         if constexpr (R < 16 * RT) {  // zero columns R..16 RT-1
-          constexpr int ZQ = (16 * RT - R) / 4;
-          for (int i = tid; i < K * ZQ; i += 256)
-            *reinterpret_cast<float4*>(&OmL[(i / ZQ) * OPJ + R + 4 * (i % ZQ)]) = make_float4(0.f, 0.f, 0.f, 0.f);
+          for (int i = tid; i < (16 * RT - R) * OPK / 4; i += 256)
+            *reinterpret_cast<float4*>(&OmL[R * OPK + 4 * i]) = make_float4(0.f, 0.f, 0.f, 0.f);
         }
       }
     }
@@ -683,8 +751,14 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
           for (int m = 0; m < VR; ++m) vsv[m] = vr[gq].get(m);
         }
 #pragma unroll
-        for (int m = 0; m < KPL; m += 4)
-          *reinterpret_cast<float4*>(&Ls[s * LP + col * KPL + m]) = make_float4(ksv[m], ksv[m + 1], ksv[m + 2], ksv[m + 3]);
+        for (int m = 0; m < KPL; ++m) Ls[slot_row<SP>(col * KPL + m) + s] = ksv[m];
+        if constexpr (ERASE && !CHAN) {  // <k_s, k_n>, s < n, while the keys are in registers
+          float d = 0.f;
+#pragma unroll
+          for (int m = 0; m < KPL; ++m) d += ksv[m] * knr.get(m);
+          d = row_sum16(d);
+          if (col == 0) dl[s] = d;
+        }
 #pragma unroll
         for (int m = 0; m < VR; m += 4)
           *reinterpret_cast<float4*>(&Us[s * UP + col * VR + m]) = make_float4(vsv[m], vsv[m + 1], vsv[m + 2], vsv[m + 3]);
@@ -721,8 +795,13 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
         const float gnn = __shfl(g, n);
         if (sl < SP) {
           bsl[sl] = live ? bl : 0.f;
-          gsl[sl] = live ? g : 0.f;
-          if constexpr (!CHAN) csc[sl] = live ? fast_exp(gnn - g) : 0.f;
+          if constexpr (!CHAN) {
+            csc[sl] = live ? fast_exp(gnn - g) : 0.f;
+            bel[sl] = live ? bl * fast_exp(g) : 0.f;
+          }
+        }
+        if constexpr (!CHAN) {
+          if (sl == 0) egl[0] = fast_exp(gnn);
         }
       }
       if constexpr (ERASE) {
@@ -734,130 +813,103 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
       }
     }
     lds_barrier();
-    if (flush) {  // the current slot's scalars, for every thread
-      gn = gsl[n];
-      bn = bsl[n];
-      if constexpr (!CHAN) egn = fast_exp(gn);
+    if constexpr (STATE_LATE) {
+      load_state();
+      compiler_fence();
     }
-
     if (flush) {
+      if constexpr (!CHAN) egn = egl[0];
       if constexpr (ERASE) {
-        // ---- channel work: thread tid owns channel k = tid.  Ls holds raw keys.
-        // The pseudo-values of slots before n need only the stored rows of T^{-1},
-        // so the waves that own no channel form them meanwhile.
-        static_assert(K + V <= 256, "channel waves and value waves must be disjoint");
-        float pi[SP], kn = 0.f;
-        if (tid < K) {
-          const int kk = tid;
-          kn = Ls[n * LP + kk];
-          float gnk = gn;
-          if constexpr (CHAN) {
-            // g_s of channel tid: running sum of the chunk's log alphas
-            float acc = 0.f;
-#pragma unroll
-            for (int s = 0; s < SP; ++s) {
-              acc += s <= n ? gk[s] : 0.f;
-              gk[s] = s <= n ? acc : 0.f;
-            }
-#pragma unroll
-            for (int s = 0; s < SP; ++s)
-              if (s == n) gnk = gk[s];
-          }
-          // erase factors pi_s = sum_{j<=s} (T^{-1})_{s,j} beta_j e^{g_j} k_j, s < n
-          // (eq. wy with T^{-1} from the ring): independent sums, no recursion
-          float xk[SP];
-#pragma unroll
-          for (int s = 0; s < SP; ++s) xk[s] = s < n ? bsl[s] * fast_exp(CHAN ? gk[s] : gsl[s]) * Ls[s * LP + kk] : 0.f;
+        // ---- the channel work: Pi = T^{-1} (beta . e^g . k) and the A operand
+        // of u = T^{-1} (beta . v), for all slots at once on the matrix cores.
+        // Rows of T^{-1} past slot n and keys past it are zero in LDS, so no
+        // slot needs a branch (one per slot, as n is a run-time value, had each
+        // LDS read wait for the one before: 4.1 of the 12.9 us a GDN item takes
+        // alone on a CU, against about 0.5 us now).
+        constexpr int KQT = (MT + 3) / 4;  // channel tiles per wave
+        [[maybe_unused]] floatx4 xb[KQT];  // KDA: e^{g_j} . k_j, j = 4 lg .., of channel 16 kt + lr
+        if constexpr (CHAN) {
+          // thread: channel k, the slots of one of 256 / K groups (wave-uniform)
+          constexpr int NGRP = 256 / K, SPG = SP / NGRP;
+          const int k = tid % K;
+          float acc = 0.f;  // g_s: running sum of the chunk's log alphas
 #pragma unroll
           for (int s = 0; s < SP; ++s) {
-            pi[s] = 0.f;
-            if (s < n) {
-              float acc = xk[s];
+            acc += s <= n ? gk[s] : 0.f;
+            gk[s] = acc;
+          }
+          if (tid < K) ds[k] = fast_exp(acc);
 #pragma unroll
-              for (int j = 0; j < s; ++j) acc += Bs[s * SP + j] * xk[j];
-              pi[s] = acc;
+          for (int g = 0; g < NGRP; ++g) {
+            if (wave / (4 / NGRP) != g) continue;
+#pragma unroll
+            for (int s = SPG * g; s < SPG * (g + 1); s += 4) {
+              float* lp = &Ls[slot_row<SP>(k) + s];
+              const floatx4 kk = lds4(lp);
+              floatx4 l, x;
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {  // (keys past slot n are zero)
+                l[i] = s + i < n ? kk[i] * fast_exp(acc - gk[s + i]) : kk[i];
+                x[i] = kk[i] * fast_exp(gk[s + i]);
+              }
+              *reinterpret_cast<float4*>(lp) = make_float4(l[0], l[1], l[2], l[3]);
+              *reinterpret_cast<float4*>(&Pi[slot_row<SP>(k) + s]) = make_float4(x[0], x[1], x[2], x[3]);
             }
           }
-          // b_{n,s} = <exp(g_n - g_s) . k_s, k_n>: partial sums over this wave's channels
+          lds_barrier();
+          // b_{n,s} = <L[s], k_n> (L[n] = k_n): one slot per 16 lanes
+          float d = 0.f;
 #pragma unroll
-          for (int s = 0; s < SP; ++s) {
-            if (s < n) {
-              const float e = CHAN ? fast_exp(gnk - gk[s]) : csc[s];
-              const float bsum = wave_sum(e * Ls[s * LP + kk] * kn);
-              if (lane == 0) bpart[wave * SP + s] = bsum;
-            }
+          for (int m = 0; m < K / 16; ++m) {
+            const float* lp = &Ls[slot_row<SP>(col + 16 * m)];
+            d += lp[4 * wave + row] * lp[n];
           }
-          if constexpr (CHAN) {
-            // left factors L[s] = exp(g_n - g_s) k_s replace the keys in place
-            ds[kk] = fast_exp(gnk);
+          d = row_sum16(d);
+          if (col == 0) dl[4 * wave + row] = d;
 #pragma unroll
-            for (int s = 0; s < SP; ++s)
-              if (s < n) Ls[s * LP + kk] *= fast_exp(gnk - gk[s]);
-          }
-        } else if (tid >= 256 - V) {
-          // pseudo-values u_s = sum_{j<=s} (T^{-1})_{s,j} beta_j v_j, s < n, in
-          // place over the raw values (thread owns value channel v)
-          const int v = tid - (256 - V);
-          float xv[SP];
-#pragma unroll
-          for (int s = 0; s < SP; ++s) xv[s] = s < n ? bsl[s] * Us[s * UP + v] : 0.f;
-#pragma unroll
-          for (int s = 0; s < SP; ++s) {
-            if (s < n) {
-              float acc = xv[s];
-#pragma unroll
-              for (int j = 0; j < s; ++j) acc += Bs[s * SP + j] * xv[j];
-              Us[s * UP + v] = acc;
-            }
-          }
+          for (int q = 0; q < KQT; ++q)
+            if (wave + 4 * q < MT) xb[q] = lds4(&Pi[slot_row<SP>(16 * (wave + 4 * q) + lr) + 4 * lg]);
+          lds_barrier();  // Pi takes the place of e^g . k
         }
-        lds_barrier();
-        // ---- slot n: row n of the couplings comes from every wave's partial sums
-        if (tid < V) {
-          const int v = tid;
-          float acc = Us[n * UP + v];
+        // row lr of T^{-1}, columns 4 lg ..: the stored rows, and row n =
+        // -beta_n b_{n,.} T^{-1} (row n of T T^{-1} = I)
+        floatx4 tr = lds4(&Bs[lr * SP + 4 * lg]);
+        const float bl_n = lr < n ? dl[lr] * (CHAN ? 1.f : csc[lr]) : 0.f;
+        const float bn = bsl[n];
 #pragma unroll
-          for (int j = 0; j < SP; ++j) {
-            if (j < n) {
-              float bj = 0.f;
-#pragma unroll
-              for (int w = 0; w < KW; ++w) bj += bpart[w * SP + j];
-              acc -= bj * Us[j * UP + v];
-            }
-          }
-          Us[n * UP + v] = bn * acc;
+        for (int i = 0; i < 4; ++i) {
+          const int j = 4 * lg + i;
+          if (j == lr && lr <= n) tr[i] = 1.f;
+          const float p = row_sum16(bl_n * tr[i]);  // sum_s b_{n,s} (T^{-1})_{s,j}
+          if (lr == n && j < n) tr[i] = -bn * p;
         }
-        if (tid < K) {
-          const int kk = tid;
-          float gnk = gn;
-          if constexpr (CHAN) {
+        const floatx4 be = lds4(&(CHAN ? bsl : bel)[4 * lg]), bb = lds4(&bsl[4 * lg]);
+        floatx4 tp;
 #pragma unroll
-            for (int s = 0; s < SP; ++s)
-              if (s == n) gnk = gk[s];
+        for (int i = 0; i < 4; ++i) {
+          tp[i] = -tr[i] * be[i];
+          tu[i] = tr[i] * bb[i];
+        }
+#pragma unroll
+        for (int q = 0; q < KQT; ++q) {
+          const int kt = wave + 4 * q;
+          if (kt < MT) {
+            floatx4 x;
+            if constexpr (CHAN) x = xb[q];
+            else x = lds4(&Ls[slot_row<SP>(16 * kt + lr) + 4 * lg]);
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc = mfma4(tp[i], x[i], acc);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) Pi[(4 * lg + i) * LP + 16 * kt + lr] = acc[i];
           }
-          float acc = fast_exp(gnk) * kn;
-#pragma unroll
-          for (int j = 0; j < SP; ++j) {
-            if (j < n) {
-              float bj = 0.f;
-#pragma unroll
-              for (int w = 0; w < KW; ++w) bj += bpart[w * SP + j];
-              acc -= bj * pi[j];
-            }
-          }
-          const float pin = bn * acc;
-#pragma unroll
-          for (int s = 0; s < SP; ++s) PiT[kk * PP + s] = (s < n) ? pi[s] : (s == n ? pin : 0.f);
         }
         lds_barrier();
       }
     }
     if (last) break;
     // an earlier chunk: its update, before the next chunk's staging reuses the LDS
-#pragma unroll
-    for (int t = 0; t < VTW; ++t)
-      if (wave + 4 * t < VT)
-        rank_update_tile<KIND, MT, ST, LP, PP, UP>(xs[t], 16 * (wave + 4 * t) + lr, lr, lg, egn, Ls, PiT, Us, bsl, csc, ds);
+    rank_update<KIND, MT, ST, VTW, LP, UP, NCW>(xs, wave, lr, lg, egn, Ls, Pi, Us, tu, bsl, csc, ds);
     lds_barrier();
   }
 
@@ -886,59 +938,72 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
     msc = m > 0.f ? ldexpf(1.f, -e) : 1.f;
   }
   }
+  if (ps == 0) {
+    if (flush) {
+      rank_update<KIND, MT, ST, VTW, LP, UP, NCW>(xs, wave, lr, lg, egn, Ls, Pi, Us, tu, bsl, csc, ds);
 #pragma unroll
-  for (int t = 0; t < VTW; ++t) {
-    const int vt = wave + 4 * t;
-    if (vt >= VT) continue;
-    const int v = 16 * vt + lr;
-    if (flush && ps == 0) {
-      rank_update_tile<KIND, MT, ST, LP, PP, UP>(xs[t], v, lr, lg, egn, Ls, PiT, Us, bsl, csc, ds);
-      // exact output o_W[v] = sum_k X_W[v][k] q_W[k]
-      if (a.o) {
-        float p = 0.f;
+      for (int t = 0; t < VTW; ++t) {
+        const int vt = wave + 4 * t, v = 16 * vt + lr;
+        // exact output o_W[v] = sum_k X_W[v][k] q_W[k]
+        if (a.o) {
+          float p = 0.f;
 #pragma unroll
-        for (int kt = 0; kt < MT; ++kt)
+          for (int kt = 0; kt < MT; ++kt) {
+            const floatx4 q4 = lds4(&qs[16 * kt + 4 * lg]);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) p += xs[t][kt][i] * qs[16 * kt + 4 * lg + i];
-        p = cross_row_sum(p);
-        if (lg == 0) a.o[item * V + v] = p;
-      }
-      // the state is final: store it before the sketch and map products
-      {
+            for (int i = 0; i < 4; ++i) p += xs[t][kt][i] * q4[i];
+          }
+          p = cross_row_sum(p);
+          if (lg == 0) a.o[item * V + v] = p;
+        }
+        // the state is final: store it before the sketch and map products
         float* dst = a.S + item * V * K + (size_t)(vt * MT) * 256 + 4 * lane;
 #pragma unroll
         for (int kt = 0; kt < MT; ++kt)
           st_nt(reinterpret_cast<float4*>(dst + 256 * kt), make_float4(xs[t][kt][0], xs[t][kt][1], xs[t][kt][2], xs[t][kt][3]));
       }
     }
-    if constexpr (P != 0) {
-      if (ps == 0) {  // the tile is final (updated, or as loaded for the initial sketch)
+    if constexpr (P != 0) {  // the tiles are final (updated, or as loaded for the initial sketch)
+#pragma unroll
+      for (int t = 0; t < VTW; ++t)
 #pragma unroll
         for (int kt = 0; kt < MT; ++kt)
 #pragma unroll
           for (int i = 0; i < 4; ++i) xmax = fmaxf(xmax, fabsf(xs[t][kt][i]));
-      }
     }
-    // sketch U^T = Omega^T X^T  (rows j = 16 jt + 4 lg + i of the C layout)
-    if constexpr (R > 0) {
-      if (want_U && ps == PASSES - 1) {
-        const float* om = a.omega + (size_t)h * K * R;
-        float aop[4] = {0.f, 0.f, 0.f, 0.f};            // U_p^T (exact: U^T) as the A operand of N^T = U_p^T X
+  }
+  // sketch U^T = Omega^T X^T  (rows j = 16 jt + 4 lg + i of the C layout)
+  if constexpr (R > 0) {
+    if (want_U && ps == PASSES - 1) {
+      const float* om = a.omega + (size_t)h * K * R;
+      float aop[VTW][4];                              // U_p^T (exact: U^T) as the A operand of N^T = U_p^T X
 #pragma unroll
-        for (int jt = 0; jt < RT; ++jt) {
-          const int jj = 16 * jt + lr;
-          floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+      for (int jt = 0; jt < RT; ++jt) {
+        const int jj = 16 * jt + lr;
+        floatx4 uc[VTW][NCU];
 #pragma unroll
-          for (int kt = 0; kt < MT; ++kt)
+        for (int t = 0; t < VTW; ++t)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              float w;
-              if constexpr (OM_LDS)
-                w = OmL[(16 * kt + 4 * lg + i) * OPJ + jj];
-              else
-                w = (jj < R) ? om[(16 * kt + 4 * lg + i) * R + jj] : 0.f;
-              acc = mfma4(w, xs[t][kt][i], acc);
-            }
+          for (int e = 0; e < NCU; ++e) uc[t][e] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kt = 0; kt < MT; ++kt) {
+          floatx4 w;
+          if constexpr (OM_LDS) {
+            w = lds4(&OmL[jj * OPK + 16 * kt + 4 * lg]);
+          } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = (jj < R) ? om[(16 * kt + 4 * lg + i) * R + jj] : 0.f;
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int t = 0; t < VTW; ++t) uc[t][i % NCU] = mfma4(w[i], xs[t][kt][i], uc[t][i % NCU]);
+        }
+#pragma unroll
+        for (int t = 0; t < VTW; ++t) {
+          const int v = 16 * (wave + 4 * t) + lr;
+          floatx4 acc = uc[t][0];
+          if constexpr (NCU == 2) acc += uc[t][1];
           if constexpr (P != 0) {
             // every sketch column of the tile's 16 values goes through LDS, so
             // that U^T becomes an operand with the value index as the
@@ -955,7 +1020,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
               // the whole Gram U^T U (R <= 16: one block)
 #pragma unroll
               for (int st = 0; st < 4; ++st) {
-                aop[st] = ut[st];
+                aop[t][st] = ut[st];
                 gacc = mfma4(ut[st], ut[st], gacc);
               }
             } else {
@@ -963,11 +1028,11 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
               // jt = 0) on the matrix cores, and the squared columns
               if (jt == 0) {
 #pragma unroll
-                for (int st = 0; st < 4; ++st) aop[st] = lr < P ? ut[st] : 0.f;
+                for (int st = 0; st < 4; ++st) aop[t][st] = lr < P ? ut[st] : 0.f;
               }
 #pragma unroll
               for (int st = 0; st < 4; ++st) {
-                gram[jt] = mfma4(ut[st], aop[st], gram[jt]);
+                gram[jt] = mfma4(ut[st], aop[t][st], gram[jt]);
                 dsq[jt] += ut[st] * ut[st];
               }
             }
@@ -988,7 +1053,10 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
             }
           }
         }
-        if constexpr (P != 0) {
+      }
+      if constexpr (P != 0) {
+#pragma unroll
+        for (int t = 0; t < VTW; ++t) {
           // N^T = U_p^T X (exact map: U^T X) over this tile's 16 values on the matrix cores: each 16 x 16
           // block of X goes through LDS so that the value index becomes the
           // contraction index (lane group), then four 16x16x4 steps
@@ -1001,7 +1069,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
             *reinterpret_cast<float4*>(&cx[lr * XP + 4 * lg]) = xsc;
             wave_lds_sync();
 #pragma unroll
-            for (int st = 0; st < 4; ++st) nacc[kt] = mfma4(aop[st], cx[(4 * st + lg) * XP + lr], nacc[kt]);
+            for (int st = 0; st < 4; ++st) nacc[kt] = mfma4(aop[t][st], cx[(4 * st + lg) * XP + lr], nacc[kt]);
             // one accumulation per element (a four-term sum here keeps the scaled
             // values live across the syncs: 22 more registers for Mamba-2)
 #pragma unroll
@@ -1015,7 +1083,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
 
   if constexpr (P > 0) {
     if (want_U)
-      coef_map_tail<K, R, P, MT, RT, SP * LP, SP * UP, OPJ, SK>(a, item, wave, lane, tid, rh, nacc, gram, dsq, msq, Ls, Us,
+      coef_map_tail<K, R, P, MT, RT, LSZ, SP * UP, OPK, SK>(a, item, wave, lane, tid, rh, nacc, gram, dsq, msq, Ls, Us,
                                                                  cmS, OmL, cmF);
   }
   if constexpr (EXACT) {

@@ -50,7 +50,12 @@ constexpr int flush_cap(int kind, int K, int V) {
   if (kind != MAMBA2) return kb >= 64 ? 3 : 0;
   return kb >= 64 ? 2 : kb >= 32 ? 3 : 5;
 }
-constexpr int kTokenPerCU = 2;
+// Bytes of state in flight per CU of the single-token update, whose workgroups
+// are one 16-value tile each (us at four / five / six / eight tiles of 8 KB and
+// uncapped, 1 GiB of state: GDN K = V = 128 332 / 322 / 329 / 346 / 353, Mamba-2
+// K = 128, V = 64 332 / 340 / 345 / 360 / 348; at eight / ten / twelve tiles of
+// 4 KB and uncapped: GDN K = V = 64 334 / 329 / 333 / 346).
+constexpr int kTokenBytesPerCU = 40 * 1024;
 
 template <int KIND, int K, int V, int R, int WM, typename IO, typename SK, int P, bool APPEND>
 int launch_decode_as(const DecodeArgs& a, hipStream_t s) {
@@ -151,11 +156,9 @@ int run_full_read(const DecodeArgs& a, int K, int V, int io, void* stream) {
 
 template <int KIND, int K, int V, typename IO>
 int launch_token(const UpdateArgs& a, hipStream_t s) {
-  const size_t items = (size_t)a.B * a.H;
-  // (the erase families' single-token update holds more registers per lane and
-  // measured the same at two to five resident workgroups per CU)
-  static const size_t cap = KIND == MAMBA2 ? lds_for_cap(&token_kernel<KIND, K, V, IO>, kTokenPerCU) : 0;
-  hipLaunchKernelGGL((token_kernel<KIND, K, V, IO>), dim3((unsigned)items), dim3(256), cap, s, a);
+  const size_t tiles = (size_t)a.B * a.H * (V / 16);  // < 2^26 (the ABI bounds B*H)
+  static const size_t cap = lds_for_cap(&token_kernel<KIND, K, V, IO>, kTokenBytesPerCU / (64 * K));
+  hipLaunchKernelGGL((token_kernel<KIND, K, V, IO>), dim3((unsigned)tiles), dim3(64), cap, s, a);
   return 0;
 }
 

@@ -1105,121 +1105,112 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
 // one cross-row sum.  In X's terms the update is
 //   X <- X Diag(alpha) + beta (v - X Diag(alpha) k) k^T     (GDN, KDA)
 //   X <- alpha X + beta v k^T                               (Mamba-2).
+//
+// What bounds it: the in-place stream, whose rate depends on how many bytes a
+// CU has in flight between their load and their store.  A probe that rewrites
+// 1 GiB in place reached 6.8 TB/s with about 32 KB in flight per CU (8 MB over
+// the chip), 5.3 to 5.5 with two or more 64 KB items per CU, and 6.2 with twice
+// the bytes in the same 8 KB pieces.  So a workgroup is one wave with one
+// 16-value tile (8 KB at K = 128), the launch holds about 40 KB of them per CU
+// (kTokenBytesPerCU), and no wave waits for another.  At 1 GiB of state, against
+// one workgroup of four waves per item (its best cap): GDN K = V = 128 406 ->
+// 322 us, KDA 403 -> 322, Mamba-2 K = 128, V = 64 350 -> 338, GDN K = 128, V = 64
+// 342 -> 331, K = V = 64 336 -> 329 (GDN).  Two or four tiles a wave: 330, 349.
+// The tiles of an item go to workgroups of the same XCD (round robin over
+// eight items), so that its k, q and decays are fetched once: 337 -> 322 us.
 template <int KIND, int K, int V, typename IO>
-__global__ __launch_bounds__(256) void token_kernel(const UpdateArgs a) {
+__global__ __launch_bounds__(64) void token_kernel(const UpdateArgs a) {
   constexpr bool ERASE = KIND != MAMBA2;
   constexpr bool CHAN = KIND == KDA;
-  constexpr int MT = K / 16, VT = V / 16, VTW = (VT + 3) / 4;
+  constexpr int MT = K / 16, VT = V / 16;
+  constexpr int C = K / 64;                          // key channels per lane
   __shared__ __align__(16) float ks[K];              // k
   __shared__ __align__(16) float qs[K];              // q
   __shared__ __align__(16) float as[CHAN ? K : 4];   // per-channel decay alpha (KDA)
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lr = lane & 15, lg = lane >> 4;
-  const size_t item = blockIdx.x;                    // b * H + h
+  const int lane = threadIdx.x, lr = lane & 15, lg = lane >> 4;
+  // workgroup -> (item, tile): groups of eight items, one per XCD; the last
+  // items, where fewer than eight are left, in plain order
+  const uint32_t NI = gridDim.x / VT, wg = blockIdx.x, full = NI / 8 * 8;
+  uint32_t it, vt;
+  if (wg < full * VT) {
+    const uint32_t j = wg >> 3;
+    it = j / VT * 8 + (wg & 7);
+    vt = j % VT;
+  } else {
+    it = wg / VT;
+    vt = wg % VT;
+  }
+  const size_t item = it;                            // b * H + h
   // the token's raw inputs: its ring slot, or its own arrays (then appended)
   const bool own = a.tk != nullptr;
   const size_t slot = item * (size_t)a.W + a.n, cur = own ? item : slot;
-  const IO* tk = static_cast<const IO*>(own ? a.tk : a.rk);
-  const IO* tv = static_cast<const IO*>(own ? a.tv : a.rv);
-  const float* tla = own ? a.tla : a.rla;
 
-  // ---- the token's small loads, then the single read of the state
-  float kk = 0.f, qq = 0.f, lk = 0.f;
-  if (tid < K) {
-    kk = load1<IO>(tk + cur * K + tid);
-    qq = load1<IO>(static_cast<const IO*>(a.q) + item * K + tid);
-    if constexpr (CHAN) lk = tla[cur * K + tid];
-  }
+  // ---- the token's small loads, then the tile's single read
+  Raw<IO, C> kr, qr;
+  kr.load(static_cast<const IO*>(own ? a.tk : a.rk) + cur * K + lane * C);
+  qr.load(static_cast<const IO*>(a.q) + item * K + lane * C);
+  const float* la = own ? a.tla : a.rla;
+  Raw<float, CHAN ? C : 1> lr_raw;
+  lr_raw.load(CHAN ? la + cur * K + lane * C : la + cur);
   const float beta = (own ? a.tbeta : a.rbeta)[cur];
-  const float ls = CHAN ? 0.f : tla[cur];
-  float vv[VTW];
+  const float vv = load1<IO>(static_cast<const IO*>(own ? a.tv : a.rv) + cur * V + 16 * vt + lr);
+  float* S = a.S + item * V * K + (size_t)(vt * MT) * 256 + 4 * lane;
+  floatx4 xs[MT];
 #pragma unroll
-  for (int t = 0; t < VTW; ++t) {
-    const int vt = wave + 4 * t;
-    vv[t] = vt < VT ? load1<IO>(tv + cur * V + 16 * vt + lr) : 0.f;
-  }
-  floatx4 xs[VTW][MT];
-#pragma unroll
-  for (int t = 0; t < VTW; ++t) {
-    const int vt = wave + 4 * t;
-    if (vt < VT) {
-      const float* src = a.S + item * V * K + (size_t)(vt * MT) * 256 + 4 * lane;
-#pragma unroll
-      for (int kt = 0; kt < MT; ++kt) {
-        const float4 x = ld_nt(reinterpret_cast<const float4*>(src + 256 * kt));
-        xs[t][kt] = floatx4{x.x, x.y, x.z, x.w};
-      }
-    }
+  for (int kt = 0; kt < MT; ++kt) {
+    const float4 x = ld_nt(reinterpret_cast<const float4*>(S + 256 * kt));
+    xs[kt] = floatx4{x.x, x.y, x.z, x.w};
   }
   compiler_fence();
-  if (tid < K) {
-    ks[tid] = kk;
-    qs[tid] = qq;
-    if constexpr (CHAN) as[tid] = fast_exp(lk);
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    ks[lane * C + c] = kr.get(c);
+    qs[lane * C + c] = qr.get(c);
+    if constexpr (CHAN) as[lane * C + c] = fast_exp(lr_raw.get(c));
   }
-  if (own) {  // append the token to the ring (io values round-trip through fp32 exactly)
-    if (tid < K) {
-      st_elem<IO>(const_cast<IO*>(static_cast<const IO*>(a.rk)) + slot * K + tid, kk);
-      if constexpr (CHAN) const_cast<float*>(a.rla)[slot * K + tid] = lk;
-    }
-#pragma unroll
-    for (int t = 0; t < VTW; ++t)
-      if (lg == 0 && wave + 4 * t < VT)
-        st_elem<IO>(const_cast<IO*>(static_cast<const IO*>(a.rv)) + slot * V + 16 * (wave + 4 * t) + lr, vv[t]);
-    if (tid == 0) {
-      const_cast<float*>(a.rbeta)[slot] = beta;
-      if constexpr (!CHAN) const_cast<float*>(a.rla)[slot] = ls;
-    }
-  }
-  lds_barrier();  // LDS only: the state loads stay in flight
-  const float alpha = CHAN ? 1.f : fast_exp(ls);
-
-#pragma unroll
-  for (int t = 0; t < VTW; ++t) {
-    const int vt = wave + 4 * t;
-    if (vt >= VT) continue;
-    // k, q and alpha are re-read from LDS per tile: kept in registers across
-    // the wave's tiles they would double its registers
-    compiler_fence();
-    // w = beta (v - X Diag(alpha) k), or beta v without the erase
-    float w = beta * vv[t];
-    if constexpr (ERASE) {
-      float y = 0.f;
-#pragma unroll
-      for (int kt = 0; kt < MT; ++kt) {
-        const float4 k4 = *reinterpret_cast<const float4*>(&ks[16 * kt + 4 * lg]);
-        float4 d4 = make_float4(alpha, alpha, alpha, alpha);
-        if constexpr (CHAN) d4 = *reinterpret_cast<const float4*>(&as[16 * kt + 4 * lg]);
-        y += xs[t][kt][0] * (d4.x * k4.x) + xs[t][kt][1] * (d4.y * k4.y) + xs[t][kt][2] * (d4.z * k4.z) +
-             xs[t][kt][3] * (d4.w * k4.w);
+  if (own) {  // append the token to the ring: v by every tile, the rest by the item's first
+    if (lg == 0) st_elem<IO>(const_cast<IO*>(static_cast<const IO*>(a.rv)) + slot * V + 16 * vt + lr, vv);
+    if (vt == 0) {
+      kr.store(const_cast<IO*>(static_cast<const IO*>(a.rk)) + slot * K + lane * C);
+      if constexpr (CHAN) lr_raw.store(const_cast<float*>(a.rla) + slot * K + lane * C);
+      if (lane == 0) {
+        const_cast<float*>(a.rbeta)[slot] = beta;
+        if constexpr (!CHAN) const_cast<float*>(a.rla)[slot] = lr_raw.get(0);
       }
-      w = beta * (vv[t] - cross_row_sum(y));
     }
-    compiler_fence();  // k is read again below rather than held across the cross-row sum
-    // X <- X Diag(alpha) + w k^T, then o = X q
-    float p = 0.f;
+  }
+  wave_lds_sync();
+  const float alpha = CHAN ? 1.f : fast_exp(lr_raw.get(0));
+
+  // w = beta (v - X Diag(alpha) k), or beta v without the erase
+  float w = beta * vv;
+  if constexpr (ERASE) {
+    float y = 0.f;
 #pragma unroll
     for (int kt = 0; kt < MT; ++kt) {
-      const float4 k4 = *reinterpret_cast<const float4*>(&ks[16 * kt + 4 * lg]);
-      const float4 q4 = *reinterpret_cast<const float4*>(&qs[16 * kt + 4 * lg]);
-      float4 d4 = make_float4(alpha, alpha, alpha, alpha);
-      if constexpr (CHAN) d4 = *reinterpret_cast<const float4*>(&as[16 * kt + 4 * lg]);
-      floatx4 x = xs[t][kt];
-      x[0] = x[0] * d4.x + w * k4.x;
-      x[1] = x[1] * d4.y + w * k4.y;
-      x[2] = x[2] * d4.z + w * k4.z;
-      x[3] = x[3] * d4.w + w * k4.w;
-      p += x[0] * q4.x + x[1] * q4.y + x[2] * q4.z + x[3] * q4.w;
-      xs[t][kt] = x;
+      const floatx4 k4 = lds4(&ks[16 * kt + 4 * lg]);
+      floatx4 d4 = {alpha, alpha, alpha, alpha};
+      if constexpr (CHAN) d4 = lds4(&as[16 * kt + 4 * lg]);
+      y += xs[kt][0] * (d4[0] * k4[0]) + xs[kt][1] * (d4[1] * k4[1]) + xs[kt][2] * (d4[2] * k4[2]) +
+           xs[kt][3] * (d4[3] * k4[3]);
     }
-    p = cross_row_sum(p);
-    if (a.o && lg == 0) a.o[item * V + 16 * vt + lr] = p;
-    float* dst = a.S + item * V * K + (size_t)(vt * MT) * 256 + 4 * lane;
-#pragma unroll
-    for (int kt = 0; kt < MT; ++kt)
-      st_nt(reinterpret_cast<float4*>(dst + 256 * kt), make_float4(xs[t][kt][0], xs[t][kt][1], xs[t][kt][2], xs[t][kt][3]));
+    w = beta * (vv - cross_row_sum(y));
   }
+  // X <- X Diag(alpha) + w k^T, then o = X q
+  float p = 0.f;
+#pragma unroll
+  for (int kt = 0; kt < MT; ++kt) {
+    const floatx4 k4 = lds4(&ks[16 * kt + 4 * lg]), q4 = lds4(&qs[16 * kt + 4 * lg]);
+    floatx4 d4 = {alpha, alpha, alpha, alpha};
+    if constexpr (CHAN) d4 = lds4(&as[16 * kt + 4 * lg]);
+    floatx4 x = xs[kt];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = x[i] * d4[i] + w * k4[i];
+    p += x[0] * q4[0] + x[1] * q4[1] + x[2] * q4[2] + x[3] * q4[3];
+    st_nt(reinterpret_cast<float4*>(S + 256 * kt), make_float4(x[0], x[1], x[2], x[3]));
+  }
+  p = cross_row_sum(p);
+  if (a.o && lg == 0) a.o[item * V + 16 * vt + lr] = p;
 }
 
 }  // namespace skssm

@@ -772,7 +772,7 @@ __global__ __launch_bounds__(256) void decode_kernel(const DecodeArgs a) {
           const float nb = dpp<0xB1>(ft[p]);  // quad_perm [1,0,3,2]: lane j ^ 1
           if (!(j & 1)) {
             if (j + 1 < rh)
-              reinterpret_cast<uint32_t*>(dst)[j >> 1] = bf16_bits_rne(ft[p]) | (bf16_bits_rne(nb) << 16);
+              reinterpret_cast<uint32_t*>(dst)[j >> 1] = bf16_pack2(ft[p], nb);
             else if (j < rh)
               st_elem<SK>(dst + j, ft[p]);
           }

@@ -64,13 +64,17 @@ template <> __device__ __forceinline__ void st_bits<float>(float* p, uint32_t of
 template <> __device__ __forceinline__ void st_bits<bf16_t>(bf16_t* p, uint32_t off, uint32_t x) {
   p[off] = (bf16_t)x;
 }
-// fp32 -> bf16 bits, round to nearest with ties to even (NaN payloads are
-// truncated, infinities kept).
-__device__ __forceinline__ uint32_t bf16_bits_rne(float x) {
-  uint32_t u = __float_as_uint(x);
-  if ((u & 0x7f800000u) != 0x7f800000u) u += 0x7fffu + ((u >> 16) & 1u);
-  return u >> 16;
+// fp32 -> bf16 bits, round to nearest with ties to even (v_cvt_pk_bf16_f32):
+// two values, the first in the low half, or one.  The same rounding in integer
+// arithmetic takes seven instructions a value; the flush that builds a rank-32
+// map converts 6,144 values an item and shares its vector units with the
+// matrix cores' operands.
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t bf16_pack2(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{lo, hi}, bf16x2));
 }
+__device__ __forceinline__ uint32_t bf16_bits_rne(float x) { return bf16_pack2(x, 0.f) & 0xFFFFu; }
 
 // One stored element of a field kept in T (fp32, or bf16 rounded to nearest
 // even), as fp32; and four consecutive ones (16-byte / 8-byte aligned).
@@ -85,8 +89,7 @@ template <> __device__ __forceinline__ void st_elem4<float>(float* p, float a, f
   *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
 }
 template <> __device__ __forceinline__ void st_elem4<bf16_t>(bf16_t* p, float a, float b, float c, float d) {
-  *reinterpret_cast<uint2*>(p) = make_uint2(bf16_bits_rne(a) | (bf16_bits_rne(b) << 16),
-                                            bf16_bits_rne(c) | (bf16_bits_rne(d) << 16));
+  *reinterpret_cast<uint2*>(p) = make_uint2(bf16_pack2(a, b), bf16_pack2(c, d));
 }
 
 template <typename IO> __device__ __forceinline__ float bits_f32(uint32_t x) {

@@ -44,6 +44,22 @@ __device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+__device__ __forceinline__ floatx4 lds4(const float* p) {
+  const float4 t = *reinterpret_cast<const float4*>(p);
+  return floatx4{t.x, t.y, t.z, t.w};
+}
+
+// Omega^T in LDS, [sketch column j][K]: the four-channel groups of a row are
+// exchanged by its index, so that the same channels of eight columns lie in
+// different banks without padding.
+template <int K> __device__ __forceinline__ int om_at(int j, int k) { return j * K + (k ^ ((j & 7) << 2)); }
+
+// Sixteen 4 x 4 x 1 products at once, block b on lanes 4 b .. 4 b + 3:
+// c[i] of lane j += (a of lane i) (b of lane j), i and j within the quad.
+__device__ __forceinline__ floatx4 mfma4x4(float a, float b, floatx4 c) {
+  return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
+}
+
 template <typename IO> __device__ __forceinline__ float load1(const IO* p);
 template <> __device__ __forceinline__ float load1<float>(const float* p) { return *p; }
 template <> __device__ __forceinline__ float load1<bf16_t>(const bf16_t* p) { return bf16_lo((uint32_t)*p); }
@@ -69,7 +85,7 @@ template <> __device__ __forceinline__ float load1<bf16_t>(const bf16_t* p) { re
 // sketch's dtype (bf16 with the paper's storage, rounded to nearest even) in
 // 16-byte channel panels cmap[B][H][K/CPW][G][CPW].  Rows past the head's
 // rank are not stored.  Every thread of the workgroup calls this.
-template <int K, int R, int P, int MT, int RT, int LSZ, int USZ, int OPK, typename SK>
+template <int K, int R, int P, int MT, int RT, int LSZ, int USZ, typename SK>
 __device__ __forceinline__ void coef_map_tail(const UpdateArgs& a, size_t item, int wave, int lane, int tid, int rh,
                                               const floatx4 (&nacc)[MT], const floatx4 (&gram)[RT],
                                               const float (&dsq)[RT], float msq,
@@ -88,6 +104,9 @@ __device__ __forceinline__ void coef_map_tail(const UpdateArgs& a, size_t item, 
   lds_barrier();  // every wave is done with the window staging (Ls, Us), reused below
   float* cmN = Ls;  // [wave][K][P]
   float* cmG = Us;  // [wave][R][5]
+  // [R][P] -w L_G, then [R] w = D^{-1} d: behind the waves' N rows, or behind
+  // R^{-1} where those leave no room
+  float* sL = LSZ >= 4 * K * P + 5 * R ? Ls + 4 * K * P : cmS + 8 + 16;
   if (lg == 0) {
 #pragma unroll
     for (int kt = 0; kt < MT; ++kt)
@@ -212,7 +231,7 @@ __device__ __forceinline__ void coef_map_tail(const UpdateArgs& a, size_t item, 
         }
       }
     }
-    // F1 row g; L_G and w = D^{-1} d of every g for the correction M' = M - L_G^T Diag(w) Omega^T
+    // F1 row g; w = D^{-1} d and -w L_G of every g for the correction M' = M - L_G^T Diag(w) Omega^T
 #pragma unroll
     for (int c = 0; c < P; ++c) {
       float e = 0.f;
@@ -220,10 +239,9 @@ __device__ __forceinline__ void coef_map_tail(const UpdateArgs& a, size_t item, 
       for (int b = 0; b < P; ++b) e += LG[b] * Ti[b][c];
       F1[c] = dinv * e;
     }
-    float* sL = cmS + 8 + 16;  // [R][P] L_G, then [R] w = D^{-1} d
     if (g < R) {
 #pragma unroll
-      for (int c = 0; c < P; ++c) sL[g * P + c] = LG[c];
+      for (int c = 0; c < P; ++c) sL[g * P + c] = -dinv * dg * LG[c];
       sL[R * P + g] = dinv * dg;
     }
     if (lane == 0) {
@@ -235,29 +253,24 @@ __device__ __forceinline__ void coef_map_tail(const UpdateArgs& a, size_t item, 
   }
   lds_barrier();
   // M' = R^{-T} N^T / sqrt(mu) - L_G^T Diag(w) Omega^T: thread k sums the four
-  // waves' N rows for column k of M, then subtracts sum_h L_G[h] w_h Omega[k][h]
-  // (Omega's columns past the head's rank are zero in LDS, and so is w there)
-  const float* sL = cmS + 8 + 16;  // [R][P] L_G, then [R] w
+  // waves' N rows for column k of M; the correction sum_h (-w_h L_G[h][x])
+  // Omega[k][h] is one 4 x 4 x 1 product per h, a wave's 64 channels at a time
+  // (on the vector units it took five instructions per h)
   float Mk[P] = {};
-  if (tid < K) {
+  if (wave < K / 64) {
     const int k = tid;
     float Nk[P];
 #pragma unroll
     for (int b = 0; b < P; ++b)
       Nk[b] = cmN[(0 * K + k) * P + b] + cmN[(1 * K + k) * P + b] + cmN[(2 * K + k) * P + b] + cmN[(3 * K + k) * P + b];
+    floatx4 d[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int h = 0; h < R; ++h) d[h & 1] = mfma4x4(sL[P * h + (lane & 3)], OmL[om_at<K>(h, k)], d[h & 1]);
 #pragma unroll
     for (int x = 0; x < P; ++x) {
+      Mk[x] = d[0][x] + d[1][x];
 #pragma unroll
       for (int b = 0; b < P; ++b) Mk[x] += cmS[8 + b * P + x] * Nk[b];
-    }
-#pragma unroll
-    for (int h4 = 0; h4 < R; h4 += 4) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float wo = sL[R * P + h4 + e] * OmL[(h4 + e) * OPK + k];
-#pragma unroll
-        for (int x = 0; x < P; ++x) Mk[x] -= sL[(h4 + e) * P + x] * wo;
-      }
     }
   }
   lds_barrier();  // the waves' N rows are consumed: M'^T and F1 take their place
@@ -283,7 +296,7 @@ __device__ __forceinline__ void coef_map_tail(const UpdateArgs& a, size_t item, 
       floatx4 acc = {0.f, 0.f, 0.f, 0.f};
       acc = mfma4(Mb[(16 * kt + lr) * P + lg], Fb[(16 * jt + lr) * FBP + lg], acc);
       const float wj = j < R ? sL[R * P + j] : 0.f;
-      const float4 o4 = *reinterpret_cast<const float4*>(&OmL[j * OPK + k0]);
+      const float4 o4 = *reinterpret_cast<const float4*>(&OmL[om_at<K>(j, k0)]);
       acc[0] += wj * o4.x;
       acc[1] += wj * o4.y;
       acc[2] += wj * o4.z;
@@ -411,11 +424,6 @@ __device__ __forceinline__ void coef_map_exact_tail(const UpdateArgs& a, size_t 
 // every eighth row is shifted by 4 more (as do the staging writes, whose lanes
 // are 8 channels apart).
 template <int S> __device__ __forceinline__ int slot_row(int ch) { return ch * (S + 4) + (ch >> 3) * 4; }
-
-__device__ __forceinline__ floatx4 lds4(const float* p) {
-  const float4 t = *reinterpret_cast<const float4*>(p);
-  return floatx4{t.x, t.y, t.z, t.w};
-}
 
 // The rank update of a wave's 16-value tiles of X = S^T from the factors of a
 // window (or a chunk of one) in LDS, eq. wy: lane (lr, lg) holds
@@ -559,14 +567,12 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
   // fields at (s * B*H + dp) * width, dp = h * B + b
   const size_t NI = (size_t)a.B * H, dp = (size_t)h * a.B + blockIdx.x / (uint32_t)H;
 
-  // Omega^T of this head goes to LDS (one row per sketch column, rows padded so
-  // that the 16 columns of an operand read hit different banks; columns padded
-  // with zeros to whole 16-column tiles) when it is small; the full-rank case
-  // reads it from global memory.
+  // Omega^T of this head goes to LDS (om_at; columns padded with zeros to whole
+  // 16-column tiles) when it is small; the full-rank case reads it from global
+  // memory.
   constexpr bool OM_LDS = R > 0 && R <= 32;
-  constexpr int OPK = K + 4;
   constexpr int OQ = OM_LDS ? (K * R / 4 + 255) / 256 : 1;  // float4 of Omega per thread
-  __shared__ __align__(16) float OmL[OM_LDS ? 16 * RT * OPK : 4];
+  __shared__ __align__(16) float OmL[OM_LDS ? 16 * RT * K : 4];
   // this head's rank (per-head rank table): the sketch uses Omega's first rh
   // columns (the rest are zeroed in LDS, so U's columns past rh come out 0 and
   // the state-dependent map's rows past rh too); rh = 0: a dense-fallback head
@@ -589,7 +595,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
   __shared__ __align__(16) float cmXs[P != 0 && !CM_ALIAS ? 4 * 16 * XP : 4];
   float* const cmX = CM_ALIAS ? Ls : cmXs;                 // [wave][16 values][16 keys]
   float* const cmU = cmX;                                  // [wave][16 values][16 sketch columns], before X's blocks
-  __shared__ __align__(16) float cmS[P != 0 ? 8 + 16 + 5 * R : 4];  // mu parts, R^{-1}/sqrt(mu), L_G and w
+  __shared__ __align__(16) float cmS[P == 0 ? 4 : LSZ >= 16 * K + 5 * R ? 24 : 24 + 5 * R];  // mu parts, R^{-1}/sqrt(mu) (L_G and w)
   // F1 of the map, in its own LDS only where the key staging has no room
   constexpr bool CMF_OWN = P > 0 && LSZ < P * K + 16 * RT * (P + 1);
   __shared__ __align__(16) float cmF[CMF_OWN ? 16 * RT * (P + 1) : 4];
@@ -725,12 +731,12 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
             for (int e = 0; e < 4; ++e)
               if (4 * (i % (R / 4)) + e >= rh) w.e[e] = 0.f;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) OmL[(4 * (i % (R / 4)) + e) * OPK + i / (R / 4)] = w.e[e];
+            for (int e = 0; e < 4; ++e) OmL[om_at<K>(4 * (i % (R / 4)) + e, i / (R / 4))] = w.e[e];
           }
         }
         if constexpr (R < 16 * RT) {  // zero columns R..16 RT-1
-          for (int i = tid; i < (16 * RT - R) * OPK / 4; i += 256)
-            *reinterpret_cast<float4*>(&OmL[R * OPK + 4 * i]) = make_float4(0.f, 0.f, 0.f, 0.f);
+          for (int i = tid; i < (16 * RT - R) * K / 4; i += 256)
+            *reinterpret_cast<float4*>(&OmL[R * K + 4 * i]) = make_float4(0.f, 0.f, 0.f, 0.f);
         }
       }
     }
@@ -989,7 +995,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
         for (int kt = 0; kt < MT; ++kt) {
           floatx4 w;
           if constexpr (OM_LDS) {
-            w = lds4(&OmL[jj * OPK + 16 * kt + 4 * lg]);
+            w = lds4(&OmL[om_at<K>(jj, 16 * kt + 4 * lg)]);
           } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i) w[i] = (jj < R) ? om[(16 * kt + 4 * lg + i) * R + jj] : 0.f;
@@ -1047,9 +1053,8 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
             if constexpr (sizeof(SK) == 4) {
               reinterpret_cast<float4*>(Ui)[(4 * jt + lg) * V + v] = make_float4(acc[0], acc[1], acc[2], acc[3]);
             } else {
-              const uint2 w = make_uint2(bf16_bits_rne(acc[0]) | (bf16_bits_rne(acc[1]) << 16),
-                                         bf16_bits_rne(acc[2]) | (bf16_bits_rne(acc[3]) << 16));
-              reinterpret_cast<uint2*>(Ui)[((2 * jt + (lg >> 1)) * V + v) * 2 + (lg & 1)] = w;
+              reinterpret_cast<uint2*>(Ui)[((2 * jt + (lg >> 1)) * V + v) * 2 + (lg & 1)] =
+                  make_uint2(bf16_pack2(acc[0], acc[1]), bf16_pack2(acc[2], acc[3]));
             }
           }
         }
@@ -1083,7 +1088,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
 
   if constexpr (P > 0) {
     if (want_U)
-      coef_map_tail<K, R, P, MT, RT, LSZ, SP * UP, OPK, SK>(a, item, wave, lane, tid, rh, nacc, gram, dsq, msq, Ls, Us,
+      coef_map_tail<K, R, P, MT, RT, LSZ, SP * UP, SK>(a, item, wave, lane, tid, rh, nacc, gram, dsq, msq, Ls, Us,
                                                                  cmS, OmL, cmF);
   }
   if constexpr (EXACT) {

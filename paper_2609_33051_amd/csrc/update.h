@@ -516,8 +516,12 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
   // accumulation chains per tile of X_0 Pi^T and of the sketch: more chains
   // shorten the dependent sums (and round less), two tiles' worth of four spill
   // where the map's bound leaves 128 registers (KDA, P = 4: 132 bytes per lane)
-  constexpr int NCW = P == 0 || VTW == 1 ? 4 : 2;
-  constexpr int NCU = P == 0 || VTW == 1 ? 2 : 1;
+  // and where a window of two chunks holds the state through the second's
+  // staging (KDA, W = 32, rank 32, B = 256: 44 bytes and 422 us, with two
+  // chains 12 bytes and 397 us)
+  constexpr bool DEEP = (P == 0 && CH == 1) || VTW == 1;
+  constexpr int NCW = DEEP ? 4 : 2;
+  constexpr int NCU = DEEP ? 2 : 1;
   constexpr int KPL = K / 16;         // key channels per lane (row layout)
   constexpr int VR = V / 16;          // value channels per lane (row layout)
   constexpr int LP = K + 4;           // LDS pitches chosen so that the 4 lane

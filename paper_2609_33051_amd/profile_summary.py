@@ -51,14 +51,15 @@ def _entry(short: str) -> str | None:
 
 def kernel_variant(short: str) -> tuple[str, str, int] | None:
     """(entry, sketch dtype, pivots) of a kernel-trace name such as
-    decode_kernel<1, 128, 128, 16, 16, unsigned short, float, 0, false>:
+    decode_kernel<1, 128, 128, 16, 16, unsigned short, float, 0, false, false>:
     update's template arguments end with io, sketch, pivots; decode's with io,
-    sketch, pivots, dense (its dense-fallback instance); full_read has no sketch."""
+    sketch, pivots and its switches (dense-fallback heads, append); full_read
+    has no sketch."""
     e = _entry(short)
     if e is None:
         return None
     targs = short[short.index("<") + 1:short.rindex(">")].split(", ")
-    if targs[-1] in ("true", "false"):
+    while targs[-1] in ("true", "false"):
         targs = targs[:-1]
     if e == "full_read":
         return e, "f32", 0

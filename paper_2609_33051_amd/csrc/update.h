@@ -313,14 +313,10 @@ __device__ __forceinline__ void coef_map_tail(const UpdateArgs& a, size_t item, 
 // The sketch pass leaves per-wave partial products of N^T = U^T X and the
 // Gram U^T U (matrix cores, contraction over the wave's value tiles) and of
 // |S|_F^2.  They are summed over the waves in LDS in a fixed order (wave 0
-// stores, waves 1..3 add in turn).  One wave inverts the G x G system (lane =
-// column of [A | I], row operations without pivoting: A is symmetric positive
-// definite with eigenvalues >= lambda), and the map is the product of the
-// inverse with N / mu on the matrix cores, G / 4 steps per 16 channels.  (A
-// Cholesky factor solved by forward and back substitution on K threads paid an
-// LDS round trip per row: the initial sketch with this map, 2,048 KDA items,
-// 49.5 us against 43.5 now.)  The dense map is stored like the pivot map's
-// (16-byte channel panels).  G <= 16.  Every thread calls this.
+// stores, waves 1..3 add in turn), the Gram system is factored by Cholesky
+// on one wave (lane = row), every channel's column of the map is solved by
+// forward and back substitution (thread k), and the dense map is stored like
+// the pivot map's (16-byte channel panels).  G <= 16.  Every thread calls this.
 template <int K, int R, typename SK>
 __device__ __forceinline__ void coef_map_exact_tail(const UpdateArgs& a, size_t item, int wave, int lane, int tid,
                                                     int rh, const floatx4 (&nacc)[K / 16], const floatx4& gacc,
@@ -328,9 +324,9 @@ __device__ __forceinline__ void coef_map_exact_tail(const UpdateArgs& a, size_t 
   constexpr int MT = K / 16, NP = K + 4, GP = R + 1;
   static_assert(R <= 16, "the exact map is compiled for ranks up to 16");
   const int lr = lane & 15, lg = lane >> 4;
-  float* Ns = Ls;            // [R][NP]   N
+  float* Ns = Ls;            // [R][NP]   N, then the map
   float* Gs = Us;            // [R][GP]   U^T U
-  float* Ai = Us + R * GP;   // [16][20]  (U^T U / mu + lambda I)^{-1} / mu, zero past R
+  float* Lm = Us + R * GP;   // [R][GP]   its Cholesky factor; then 1 / diagonal at Lm[j * GP + j]
   msq = wave_sum(msq);
   // rows j = 4 lg + i of N^T and of the Gram live in lane group lg
 #pragma unroll
@@ -360,41 +356,64 @@ __device__ __forceinline__ void coef_map_exact_tail(const UpdateArgs& a, size_t 
   const float mu = fro > 0.f ? fro / K : 1.f;
   const float imu = 1.f / mu;
   if (wave == 0) {
-    // lane c < R: column c of A = U^T U / mu + lambda I; lane 16 + c: column c of I
-    float x[R];
+    // Cholesky of A = U^T U / mu + lambda I: lane j holds row j
+    float ar[R];
 #pragma unroll
-    for (int g = 0; g < R; ++g) {
-      const float gv = lr < R ? Gs[g * GP + lr] * imu : 0.f;
-      x[g] = lane < 16 ? gv + (lane == g ? a.ridge : 0.f) : (lr == g ? 1.f : 0.f);
-    }
+    for (int g = 0; g < R; ++g) ar[g] = (lane < R ? Gs[lane * GP + g] * imu : 0.f) + (lane == g ? a.ridge : 0.f);
+    float lrow[R];
 #pragma unroll
     for (int c = 0; c < R; ++c) {
-      x[c] *= 1.f / lane_bcast(x[c], c);  // A_cc after the steps before (> 0)
+      const float piv = lane_bcast(ar[c], c);          // A_cc after the updates of columns < c (> 0: SPD)
+      const float ip = __builtin_amdgcn_rsqf(piv);
+      const float l = ar[c] * ip;                      // L_jc for j >= c
+      lrow[c] = lane >= c ? l : 0.f;
 #pragma unroll
-      for (int g = 0; g < R; ++g)
-        if (g != c) x[g] -= lane_bcast(x[g], c) * x[c];
+      for (int g = c + 1; g < R; ++g) ar[g] -= l * lane_bcast(l, g);
     }
-    if (lg == 1) {
+    if (lane < R) {
 #pragma unroll
-      for (int g = 0; g < 16; ++g) Ai[g * 20 + lr] = g < R && lr < R ? x[g < R ? g : 0] * imu : 0.f;
+      for (int c = 0; c < R; ++c) Lm[lane * GP + c] = c == lane ? 1.f / lrow[c] : lrow[c];
     }
   }
   lds_barrier();
-  // C^T = N^T A^{-1}: wave w takes k tiles w, w + 4, ...; lane (lr, lg) ends with
-  // C[lr][16 kt + 4 lg + i], i = 0..3
+  // column k of the map: L y = N_k / mu, L^T c = y.  Each row's reads of L
+  // stay within its own step (scheduling barrier): hoisting the whole
+  // triangle's reads ahead held 136 values live at rank 16 and took the
+  // kernel from 80 to 162 registers.
+  if (tid < K) {
+    const int k = tid;
+    float y[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      float e = Ns[j * NP + k] * imu;
+#pragma unroll
+      for (int c = 0; c < j; ++c) e -= Lm[j * GP + c] * y[c];
+      y[j] = e * Lm[j * GP + j];
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int j = R - 1; j >= 0; --j) {
+      float e = y[j];
+#pragma unroll
+      for (int c = j + 1; c < R; ++c) e -= Lm[c * GP + j] * y[c];
+      y[j] = e * Lm[j * GP + j];
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) Ns[j * NP + k] = y[j];
+  }
+  lds_barrier();
+  // the dense map in 16-byte channel panels: thread (kp, j), j fastest
   constexpr int CPW = 16 / (int)sizeof(SK);
   SK* cm = static_cast<SK*>(a.cmap) + item * (size_t)(R * K);
-  const floatx4 bi = lds4(&Ai[lr * 20 + 4 * lg]);  // (A^{-1})_{lr, 4 lg ..} (symmetric)
 #pragma unroll
-  for (int kq = 0; kq < MT / 4; ++kq) {
-    const int kt = wave + 4 * kq, k0 = 16 * kt + 4 * lg;
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int t = tid; t < R * K / CPW; t += 256) {
+    const int j = t % R, kp = t / R;
+    if (j < rh) {
+      const float* src = &Ns[j * NP + kp * CPW];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int g = 4 * lg + i;
-      acc = mfma4(g < R ? Ns[g * NP + 16 * kt + lr] : 0.f, bi[i], acc);
+      for (int e = 0; e < CPW; e += 4) st_elem4<SK>(cm + (size_t)t * CPW + e, src[e], src[e + 1], src[e + 2], src[e + 3]);
     }
-    if (lr < rh) st_elem4<SK>(cm + ((size_t)(k0 / CPW) * R + lr) * CPW + k0 % CPW, acc[0], acc[1], acc[2], acc[3]);
   }
 }
 
@@ -584,7 +603,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
   // F1 of the map, in its own LDS only where the key staging has no room
   constexpr bool CMF_OWN = P > 0 && LSZ < P * K + 16 * RT * (P + 1);
   __shared__ __align__(16) float cmF[CMF_OWN ? 16 * RT * (P + 1) : 4];
-  static_assert(!EXACT || (LSZ >= R * (K + 4) && SP * UP >= R * (R + 1) + 320),
+  static_assert(!EXACT || (LSZ >= R * (K + 4) && SP * UP >= 2 * R * (R + 1)),
                 "the exact map's sums must fit the window staging");
   floatx4 nacc[P != 0 ? MT : 1];   // N^T (rows 4 lg + i: pivots a < 4, or every sketch column), this wave's values
   floatx4 gram[P > 0 ? RT : 1];    // sketch Gram U^T U_p: lane (lr, lg), i: row 16 jt + 4 lg + i, column lr < P; this wave's values

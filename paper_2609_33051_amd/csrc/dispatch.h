@@ -54,8 +54,10 @@ constexpr int flush_cap(int kind, int K, int V) {
 // are one 16-value tile each (us at four / five / six / eight tiles of 8 KB and
 // uncapped, 1 GiB of state: GDN K = V = 128 332 / 322 / 329 / 346 / 353, Mamba-2
 // K = 128, V = 64 332 / 340 / 345 / 360 / 348; at eight / ten / twelve tiles of
-// 4 KB and uncapped: GDN K = V = 64 334 / 329 / 333 / 346).
-constexpr int kTokenBytesPerCU = 40 * 1024;
+// 4 KB and uncapped: GDN K = V = 64 334 / 329 / 333 / 346, Mamba-2 329 / 334 /
+// 332 / 348).  The erase families wait for the tile's product with k before
+// their first store and take a little more.
+constexpr int token_bytes_per_cu(int kind) { return (kind == MAMBA2 ? 32 : 40) * 1024; }
 
 template <int KIND, int K, int V, int R, int WM, typename IO, typename SK, int P, bool APPEND>
 int launch_decode_as(const DecodeArgs& a, hipStream_t s) {
@@ -157,7 +159,7 @@ int run_full_read(const DecodeArgs& a, int K, int V, int io, void* stream) {
 template <int KIND, int K, int V, typename IO>
 int launch_token(const UpdateArgs& a, hipStream_t s) {
   const size_t tiles = (size_t)a.B * a.H * (V / 16);  // < 2^26 (the ABI bounds B*H)
-  static const size_t cap = lds_for_cap(&token_kernel<KIND, K, V, IO>, kTokenBytesPerCU / (64 * K));
+  static const size_t cap = lds_for_cap(&token_kernel<KIND, K, V, IO>, token_bytes_per_cu(KIND) / (64 * K));
   hipLaunchKernelGGL((token_kernel<KIND, K, V, IO>), dim3((unsigned)tiles), dim3(64), cap, s, a);
   return 0;
 }

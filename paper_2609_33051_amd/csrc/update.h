@@ -513,7 +513,8 @@ __device__ __forceinline__ void rank_update(floatx4 (&x)[VTW][MT], int wave, int
 // exact) at window 16 and rank <= 16: their flush spends part of each
 // workgroup's life off the memory bus (the map's products and algebra), so
 // occupancy pays there, even with the few registers the per-channel-decay
-// instances then spill.
+// instances then spill.  (A bound of six for Mamba-2's at V = 64 spills 12 to 20
+// bytes: exact-map flush at B = 256 510 -> 543 us, P = 4 unchanged.)
 template <int KIND, int K, int V, int R, int WMAX, typename IO, typename SK, int P>
 __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) void update_kernel(const UpdateArgs a) {
   constexpr bool ERASE = KIND != MAMBA2;
@@ -1121,9 +1122,9 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
 // the chip), 5.3 to 5.5 with two or more 64 KB items per CU, and 6.2 with twice
 // the bytes in the same 8 KB pieces.  So a workgroup is one wave with one
 // 16-value tile (8 KB at K = 128), the launch holds about 40 KB of them per CU
-// (kTokenBytesPerCU), and no wave waits for another.  At 1 GiB of state, against
+// (token_bytes_per_cu), and no wave waits for another.  At 1 GiB of state, against
 // one workgroup of four waves per item (its best cap): GDN K = V = 128 406 ->
-// 322 us, KDA 403 -> 322, Mamba-2 K = 128, V = 64 350 -> 338, GDN K = 128, V = 64
+// 322 us, KDA 403 -> 322, Mamba-2 K = 128, V = 64 350 -> 332, GDN K = 128, V = 64
 // 342 -> 331, K = V = 64 336 -> 329 (GDN).  Two or four tiles a wave: 330, 349.
 // The tiles of an item go to workgroups of the same XCD (round robin over
 // eight items), so that its k, q and decays are fetched once: 337 -> 322 us.

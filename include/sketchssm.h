@@ -200,6 +200,11 @@ typedef struct {
  * o      [B][H][V] fp32 output or NULL.
  * rank may be 0 here (no sketch: the flush of the exact baseline).
  *
+ * Overlap: in this and every other reading call, o may take the place of q
+ * item for item (fp32 io, dv = dk: the same address).  A single token at rank 0
+ * whose o overlaps q or the ring's inputs runs as a window of one token, at
+ * the flush's speed.
+ *
  * Occupancy: a flush with pivots = 0 and the single-token update launch with
  * unused dynamic LDS so that only a few of their workgroups are resident per
  * CU (by the bytes of an item's state), which streams the in-place state
@@ -265,9 +270,10 @@ typedef struct {
  *   otherwise         sketchssm_decode
  * Results are bitwise those of writing the slot and making that call; the
  * kernel takes the token from its own arrays and stores it beside its other
- * work, so the append costs one write of the token and no launch.  Every
- * other argument is that call's, with its requirements (those a call does not
- * name may be NULL).  q, o and the token's arrays are required.
+ * work, so the append costs one write of the token and no launch (where o
+ * overlaps one of the token's arrays, the append is a launch before the
+ * call's).  Every other argument is that call's, with its requirements (those
+ * a call does not name may be NULL).  q, o and the token's arrays are required.
  */
 int sketchssm_step(const skssm_config* cfg, int32_t baseline, float* S, const float* omega, const float* coef,
                    const skssm_ring* ring, int32_t n_buffered, const skssm_token* token, const void* q, void* U,

@@ -135,12 +135,32 @@ int launched(int rc, const char* what) {
 }
 
 // The current token's own arrays (sketchssm_step): all required, aligned like
-// every pointer.
-int check_token(const skssm_token* t) {
+// every pointer.  The last check of a call: where o overlaps them, the token
+// is appended here by a launch of its own and the call goes on with the ring
+// (t = NULL), as no order holds between the workgroups of one launch, of which
+// some write o while others read the token.
+int take_token(const skssm_config* c, const skssm_ring* r, int32_t n, const float* o, void* stream, const skssm_token*& t) {
   if (!t->k || !t->v || !t->beta || !t->log_decay) return fail(SKSSM_EINVAL, "token k/v/beta/log_decay is NULL");
   if (!aligned(t->k) || !aligned(t->v) || !aligned(t->beta) || !aligned(t->log_decay))
     return fail(SKSSM_EALIGN, "token array not 16-byte aligned");
-  return SKSSM_OK;
+  const size_t items = (size_t)c->batch * c->heads;
+  const uint32_t io = c->io_dtype == SKSSM_BF16 ? 2 : 4;
+  const uint32_t words[4] = {c->dk * io / 4, c->dv * io / 4, 1u, c->kind == SKSSM_KDA ? (uint32_t)c->dk : 1u};
+  const void* src[4] = {t->k, t->v, t->beta, t->log_decay};
+  bool over = false;
+  for (int f = 0; f < 4; ++f) over |= skssm::overlap(o, items * c->dv * 4, src[f], items * words[f] * 4);
+  if (!over) return SKSSM_OK;
+  skssm::AppendArgs a{};
+  const void* dst[4] = {r->k, r->v, r->beta, r->log_decay};
+  for (int f = 0; f < 4; ++f) {
+    a.src[f] = static_cast<const uint32_t*>(src[f]);
+    a.dst[f] = static_cast<uint32_t*>(const_cast<void*>(dst[f]));
+    a.words[f] = words[f];
+  }
+  a.W = c->window;
+  a.n = n;
+  t = nullptr;
+  return launched(skssm::run_append_token(a, items, stream), "sketchssm_step");
 }
 
 skssm::DecodeArgs decode_args(const skssm_config* c, const skssm_ring* r, int32_t n, const skssm_token* t, const void* q,
@@ -185,8 +205,7 @@ int state_layout(const skssm_config* cfg, const float* src, float* dst, void* st
   if (!aligned(src) || !aligned(dst)) return fail(SKSSM_EALIGN, "%s: source/destination not aligned", what);
   const size_t items = (size_t)cfg->batch * cfg->heads;
   const size_t bytes = items * cfg->dk * cfg->dv * sizeof(float);
-  const uintptr_t s0 = reinterpret_cast<uintptr_t>(src), d0 = reinterpret_cast<uintptr_t>(dst);
-  if (s0 < d0 + bytes && d0 < s0 + bytes) return fail(SKSSM_EINVAL, "%s: source and destination overlap", what);
+  if (skssm::overlap(src, bytes, dst, bytes)) return fail(SKSSM_EINVAL, "%s: source and destination overlap", what);
   return launched(skssm::run_state_layout(src, dst, items, cfg->dk, cfg->dv, to_tiles, stream), what);
 }
 
@@ -224,7 +243,7 @@ int update(const skssm_config* cfg, float* S, const float* omega, const skssm_ri
       return fail(SKSSM_ESTATE, "n_buffered %d outside 0..%d", n_buffered, cfg->window - 1);
     if (!aligned(q)) return fail(SKSSM_EALIGN, "q not aligned");
     if ((rc = check_ring(cfg, ring, false, false))) return rc;
-    if (token && (rc = check_token(token))) return rc;
+    if (token && (rc = take_token(cfg, ring, n_buffered, o, stream, token))) return rc;
     if (token) {
       a.tk = token->k;
       a.tv = token->v;
@@ -281,7 +300,7 @@ int decode(const skssm_config* cfg, const void* U, const float* coef, const void
     if (!aligned(S)) return fail(SKSSM_EALIGN, "S not aligned");
   }
   if ((rc = check_ring(cfg, ring, rk.sketched > 0, rk.dense > 0))) return rc;
-  if (token && (rc = check_token(token))) return rc;
+  if (token && (rc = take_token(cfg, ring, n_buffered, o, stream, token))) return rc;
   skssm::DecodeArgs a = decode_args(cfg, ring, n_buffered, token, q, o);
   put_ranks(a, rk);
   put_order(a, rk);
@@ -310,7 +329,7 @@ int full_read(const skssm_config* cfg, const float* S, const skssm_ring* ring, i
   if (!S || !o || !q) return fail(SKSSM_EINVAL, "S, q and o are required");
   if (!aligned(S) || !aligned(o) || !aligned(q)) return fail(SKSSM_EALIGN, "S/q/o not aligned");
   if ((rc = check_ring(cfg, ring, false, true))) return rc;
-  if (token && (rc = check_token(token))) return rc;
+  if (token && (rc = take_token(cfg, ring, n_buffered, o, stream, token))) return rc;
   skssm::DecodeArgs a = decode_args(cfg, ring, n_buffered, token, q, o);
   a.S = S;
   int r;

@@ -84,6 +84,19 @@ int run_full_read_kda(const DecodeArgs& a, int K, int V, int io, void* stream);
 int run_update_mamba2(const UpdateArgs& a, int K, int V, int R, int io, int sk, int piv, void* stream);
 int run_update_gdn(const UpdateArgs& a, int K, int V, int R, int io, int sk, int piv, void* stream);
 int run_update_kda(const UpdateArgs& a, int K, int V, int R, int io, int sk, int piv, void* stream);
+// The token's arrays (k, v, beta, log decay; words[f] 4-byte words an item) into ring slot n.
+struct AppendArgs {
+  const uint32_t* src[4];         // [B][H][words]
+  uint32_t* dst[4];               // [B][H][W][words]
+  uint32_t words[4];
+  int W, n;
+};
+int run_append_token(const AppendArgs& a, size_t items, void* stream);
+// Whether two address ranges share a byte.
+inline bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + nb && y < x + na;
+}
 // State layout conversion (row layout <-> tile-major), items states of V x K.
 int run_state_layout(const float* src, float* dst, size_t items, int K, int V, int to_tiles, void* stream);
 

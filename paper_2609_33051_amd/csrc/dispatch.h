@@ -164,12 +164,27 @@ int launch_token(const UpdateArgs& a, hipStream_t s) {
   return 0;
 }
 
+// Whether a single token's update may run as token_kernel: its workgroups, one
+// per 16-value tile, each read the item's whole k, q and (KDA) decays, its
+// gates and their own values, and write their own part of o in no order among
+// themselves.  Where o takes the place of one of those arrays the window's
+// kernel runs, one workgroup per item, which has staged them before it writes.
+template <int KIND, int K, int V>
+bool tiles_independent(const UpdateArgs& a, int io) {
+  const size_t items = (size_t)a.B * a.H, slots = a.tk ? items : items * (size_t)a.W, e = io ? 2 : 4;
+  const void* in[] = {a.q, a.tk ? a.tk : a.rk, a.tk ? a.tv : a.rv, a.tk ? a.tbeta : a.rbeta, a.tk ? a.tla : a.rla};
+  const size_t bytes[] = {items * K * e, slots * K * e, slots * V * e, slots * 4, slots * (KIND == KDA ? K : 1) * 4};
+  for (int f = 0; f < 5; ++f)
+    if (overlap(a.o, items * V * 4, in[f], bytes[f])) return false;
+  return true;
+}
+
 template <int KIND, int K, int V, int R, int WM, int P>
 int update_t(const UpdateArgs& a, int io, int sk, hipStream_t s) {
   if constexpr (R == 0) {  // no sketch: its dtype does not matter
     // a single token (window-1 decoding, or a window flushed after its first
     // token): the rank-1 update streams the state through registers
-    if (a.nt == 1) return io ? launch_token<KIND, K, V, bf16_t>(a, s) : launch_token<KIND, K, V, float>(a, s);
+    if (a.nt == 1 && tiles_independent<KIND, K, V>(a, io)) return io ? launch_token<KIND, K, V, bf16_t>(a, s) : launch_token<KIND, K, V, float>(a, s);
     return io ? launch_update<KIND, K, V, 0, WM, bf16_t, float, 0>(a, s) : launch_update<KIND, K, V, 0, WM, float, float, 0>(a, s);
   } else {
     if (io) return sk ? launch_update<KIND, K, V, R, WM, bf16_t, bf16_t, P>(a, s) : launch_update<KIND, K, V, R, WM, bf16_t, float, P>(a, s);

@@ -104,3 +104,53 @@ def test_tensors_the_kernels_cannot_read_are_copied(monkeypatch):
     own = Own("gdn", 3, 3, 128, 128, 16, 8, "bf16", "cuda", omega=one.omega, coef=one.coef)
     own.step(inputs.step_inputs(wl, 0, "cuda"))
     assert own.appended == 1
+
+
+@pytest.mark.parametrize("fam", ["mamba2", "gdn", "kda"])
+@pytest.mark.parametrize("K", [64, 128])
+@pytest.mark.parametrize("W", [1, 3])
+def test_output_in_the_place_of_an_input(fam, K, W):
+    """out = the token's own q, k or v (fp32, dv = dk), through step() and, for
+    q, through read(): what an output of its own gives.  Thousands of items, so
+    that one item's workgroups need not run together.  At window 1 the two sides
+    are different kernels: fp32 sums over 128 channels in another order."""
+    wl = inputs.tiny(fam, batch=96, heads=32, dk=K, dv=K, rank=8, window=W, io="f32")
+    S = inputs.initial_state(wl, "cuda")
+    for name, through_read in (("q", False), ("q", True), ("k", False), ("v", False)):
+        one, two = (SketchSSMLayer(fam, 96, 32, K, K, 0, W, "f32", "cuda", baseline=True, S=S) for _ in range(2))
+        for t in range(W + 1):
+            inp = inputs.step_inputs(wl, t, "cuda")
+            mine = {x: y.clone() for x, y in inp.items()}
+            if through_read:
+                one.write_token(mine)
+                a = one.read(mine["q"], out=mine["q"])
+            else:
+                a = one.step(mine, out=mine[name])
+            b = two.step(inp)
+            assert float((a - b).norm() / b.norm()) < 1e-5, (name, through_read, t)
+        x, y = one.state(), two.state()
+        assert float((x - y).norm() / y.norm()) < 1e-5, (name, through_read)
+        for ring in ("rk", "rv", "rbeta", "rla"):
+            assert torch.equal(getattr(one, ring), getattr(two, ring)), (name, ring)
+
+
+@pytest.mark.parametrize("case", [CASES[0], CASES[3], CASES[7], CASES[12]], ids=lambda c: "-".join(map(str, c[:6])))
+def test_output_over_other_items_tokens(case):
+    """The output and the token's arrays in one scratch buffer, where an item's
+    output lies over other items' keys, values and gates: bitwise what separate
+    buffers give."""
+    wl, (one, two) = _pair(*case, batch=64)
+    n, (K, V, W) = 64 * 3, (case[1], case[2], case[4])
+    for t in range(W + 1):
+        inp = inputs.step_inputs(wl, t, "cuda")
+        scratch = torch.zeros(1 << 20, dtype=torch.uint8, device="cuda")
+        mine, at = {"q": inp["q"]}, 0
+        for x in ("k", "v", "log_decay", "beta"):
+            size = inp[x].numel() * inp[x].element_size()
+            mine[x] = scratch[at:at + size].view(inp[x].dtype).view(inp[x].shape)
+            mine[x].copy_(inp[x])
+            at += (size + 15) // 16 * 16
+        out = scratch[16 * (at // 48):][:n * V * 4].view(torch.float32).view(64, 3, V)
+        a = one.step(mine, out=out)
+        assert torch.equal(a, two.step(inp)), t
+    _equal(one, two)

@@ -136,6 +136,11 @@ typedef struct {
  * v = x_t, beta = dt and log_decay = dt * A_h (Sec. 3.2, M_t = D_t); the
  * query C_t is passed to each call.
  *
+ * log_decay is <= 0 and finite, except that a window's last token (the flush,
+ * the single-token update) may have -inf, alpha = 0: a later token's decays are
+ * differences of cumulative ones.  Elsewhere -104, whose exponential is 0 in
+ * fp32, stands for it.
+ *
  * Every read rebuilds the window-local cumulative log decays
  * g_s = sum_{j<=s} log alpha_j from log_decay (per channel for KDA), so every
  * decay ratio is exp(g_t - g_s) <= 1, never a division.  The library derives

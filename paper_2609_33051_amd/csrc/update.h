@@ -807,7 +807,8 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
         if (sl < SP) {
           bsl[sl] = live ? bl : 0.f;
           if constexpr (!CHAN) {
-            csc[sl] = live ? fast_exp(gnn - g) : 0.f;
+            // (c_n = 1 also where alpha_n = 0, whose log decay is -inf)
+            csc[sl] = sl == n ? 1.f : live ? fast_exp(gnn - g) : 0.f;
             bel[sl] = live ? bl * fast_exp(g) : 0.f;
           }
         }

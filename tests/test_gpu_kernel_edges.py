@@ -86,3 +86,21 @@ def test_kda_flush_that_forgets_a_channel():
         got = lay.step(tok)
     assert bool(torch.isfinite(lay.state()).all())
     assert _rel(got, o) < REL and _rel(lay.state(), X) < REL
+
+
+@pytest.mark.parametrize("kind", ["mamba2", "gdn"])
+@pytest.mark.parametrize("W", [1, 6, 16, 17, 21])
+def test_flush_that_forgets_everything(kind, W):
+    """A scalar log decay of minus infinity on the window's last token: the state
+    is that token's write alone."""
+    wl = inputs.tiny(kind, batch=2, heads=2, dk=128, dv=128, rank=16, window=W, io="f32")
+    S = inputs.initial_state(wl, "cuda")
+    lay = SketchSSMLayer(kind, 2, 2, 128, 128, 0, W, "f32", "cuda", baseline=True, S=S)
+    X = S.double()
+    for t in range(W):
+        tok = inputs.step_inputs(wl, t, "cuda")
+        if t == W - 1:
+            tok["log_decay"].fill_(float("-inf"))
+        X, o = _step64(kind, X, tok)
+        got = lay.step(tok)
+    assert _rel(got, o) < REL and _rel(lay.state(), X) < REL

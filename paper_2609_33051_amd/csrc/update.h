@@ -35,6 +35,8 @@
 // between its load and its store.
 #pragma once
 
+#include <float.h>
+
 #include "args.h"
 #include "device.h"
 
@@ -461,11 +463,25 @@ __device__ __forceinline__ void rank_update(floatx4 (&x)[VTW][MT], int wave, int
     }
 #pragma unroll
     for (int t = 0; t < VTW; ++t) {
-      floatx4 u = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) u = mfma4(tu[i], Vs[(4 * lg + i) * UP + 16 * (wave + 4 * t) + lr], u);
       wv[t][0] = pc[t][0] + pc[t][1];
       if constexpr (NC == 4) wv[t][0] += pc[t][2] + pc[t][3];
+    }
+#pragma unroll
+    for (int t = 0; t < VTW; ++t) {
+      // an infinite value enters the product as the largest finite one, whose
+      // products with the structural zeros of T^{-1} (earlier slots, slots past
+      // n) are zeros and not NaNs, and its own slot's u as it is
+      floatx4 u;
+      float vf[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int s = 4 * lg + i;
+        const float v = Vs[s * UP + 16 * (wave + 4 * t) + lr];
+        vf[i] = __builtin_amdgcn_fmed3f(v, -FLT_MAX, FLT_MAX);
+        u[i] = v - vf[i];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) u = mfma4(tu[i], vf[i], u);
       wv[t][0] += u;
       if constexpr (!CHAN) {
 #pragma unroll

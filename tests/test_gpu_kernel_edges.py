@@ -104,3 +104,28 @@ def test_flush_that_forgets_everything(kind, W):
         X, o = _step64(kind, X, tok)
         got = lay.step(tok)
     assert _rel(got, o) < REL and _rel(lay.state(), X) < REL
+
+
+@pytest.mark.parametrize("kind", ["gdn", "kda"])
+@pytest.mark.parametrize("K,V", [(64, 64), (128, 128)])
+@pytest.mark.parametrize("W", [2, 6, 16, 17, 32])
+def test_flush_with_an_infinite_value(kind, K, V, W):
+    """An infinite value on the last token reaches its own value channel as it
+    does in the recurrence (infinities with the sign of the key), with no NaN,
+    and no other channel; earlier in the window, no other channel."""
+    for slot in {W - 1, W // 2}:
+        wl = inputs.tiny(kind, batch=2, heads=2, dk=K, dv=V, rank=16, window=W, io="f32")
+        S = inputs.initial_state(wl, "cuda")
+        lay = SketchSSMLayer(kind, 2, 2, K, V, 0, W, "f32", "cuda", baseline=True, S=S)
+        X = S.double()
+        for t in range(W):
+            tok = inputs.step_inputs(wl, t, "cuda")
+            if t == slot:
+                tok["v"][..., 5] = float("inf")
+            X, o = _step64(kind, X, tok)
+            got = lay.step(tok)
+        state = lay.state()
+        rest = [i for i in range(V) if i != 5]
+        assert _rel(state[:, :, rest], X[:, :, rest]) < REL and _rel(got[..., rest], o[..., rest]) < REL
+        if slot == W - 1:
+            assert torch.equal(state[:, :, 5].double(), X[:, :, 5])

@@ -92,8 +92,6 @@ class SketchSSMLayer:
         # what a token's tensors must be for step() to hand them to the kernels as they are
         self._token_like = tuple((name, t.dtype, tuple(t.shape[:2] + t.shape[3:])) for name, t in
                                  (("k", self.rk), ("v", self.rv), ("beta", self.rbeta), ("log_decay", self.rla)))
-        cls = type(self)  # a subclass with an append or a read of its own keeps both
-        self._one_launch = cls.write_token is SketchSSMLayer.write_token and cls.read is SketchSSMLayer.read
 
     def sketch_matrix(self) -> torch.Tensor:
         """The sketch as [B][H][V][r] (a copy; U itself is stored in panels)."""
@@ -157,6 +155,12 @@ class SketchSSMLayer:
         return B.prepare_decode(self.cfg, self.U, self.coef, self.ring, n, q, o, st, cmap=self.cmap,
                                 S=self.S if self.dense_heads else None)
 
+    def _own_calls(self) -> bool:
+        """Whether write_token and read are this class's: an append or a read of
+        a subclass, or one set on the class or the instance, is called."""
+        cls, own = type(self), self.__dict__
+        return cls.write_token is _WRITE and cls.read is _READ and "write_token" not in own and "read" not in own
+
     def _as_they_are(self, inp: dict) -> bool:
         """Whether the token's tensors are laid out as the kernels read them
         (dtype, shape, contiguous, this device, 16-byte aligned)."""
@@ -175,7 +179,7 @@ class SketchSSMLayer:
         H = 32 takes 9 us as one launch against 26 us, of KDA at B = 48, H = 32
         17 us against 29 us (the copies' launches and their second pass over the
         token)."""
-        if not (self._one_launch and self._as_they_are(inp)):
+        if not (self._own_calls() and self._as_they_are(inp)):
             self.write_token(inp)
             return self.read(inp["q"], out)
         o = self.o if out is None else out
@@ -184,3 +188,6 @@ class SketchSSMLayer:
                          inp["beta"], inp["log_decay"], inp["q"], self.U, o, self.stream(), cmap=self.cmap)
         self.n = 0 if n == self.window - 1 else n + 1
         return o
+
+
+_WRITE, _READ = SketchSSMLayer.write_token, SketchSSMLayer.read

@@ -154,3 +154,22 @@ def test_output_over_other_items_tokens(case):
         a = one.step(mine, out=out)
         assert torch.equal(a, two.step(inp)), t
     _equal(one, two)
+
+
+@pytest.mark.parametrize("where", ["instance", "class"])
+@pytest.mark.parametrize("name", ["write_token", "read"])
+def test_a_replaced_append_or_read_is_called(where, name, monkeypatch):
+    """A wrapper set on a layer or on the class after its construction."""
+    wl, (one, two) = _pair("gdn", 128, 128, 16, 4, "bf16", "f32", 0, False, None)
+    calls, real = [], getattr(SketchSSMLayer, name)
+
+    def wrapper(*args, **kw):
+        calls.append(name)
+        return real(*((one,) + args if where == "instance" else args), **kw)
+
+    monkeypatch.setattr(one if where == "instance" else SketchSSMLayer, name, wrapper)
+    inp = inputs.step_inputs(wl, 0, "cuda")
+    a = one.step(inp).clone()
+    assert calls == [name]
+    monkeypatch.undo()
+    assert torch.equal(a, two.step(inp))

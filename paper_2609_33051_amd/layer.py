@@ -89,6 +89,7 @@ class SketchSSMLayer:
                                 pi=self.rpi, tinv=self.rt)
         self.o = torch.zeros((Bt, H, V), dtype=f32, device=dev)
         self.n = 0  # slot of the next token in the current window
+        self._index, self._io = self.S.get_device(), iodt
         # what a token's tensors must be for step() to hand them to the kernels as they are
         self._token_like = tuple((name, t.dtype, tuple(t.shape[:2] + t.shape[3:])) for name, t in
                                  (("k", self.rk), ("v", self.rv), ("beta", self.rbeta), ("log_decay", self.rla)))
@@ -127,7 +128,7 @@ class SketchSSMLayer:
         """One decode token whose inputs already sit in ring slot n: a non-flush
         read (sketch, or exact full read for the baseline) while the window is
         open, the flush on its W-th token."""
-        o = self.o if out is None else out
+        q, o = self._query(q), self._output(out)
         if self.n == self.window - 1:
             B.sketchssm_update(self.cfg, self.S, self.omega, self.ring, self.n, q, self.U, o, self.stream(),
                                cmap=self.cmap)
@@ -145,8 +146,11 @@ class SketchSSMLayer:
         """The read of ring slot `n` (as `read` would issue it with self.n == n)
         with its arguments marshalled once, on the current stream.  Replaying
         the W calls n = 0..W-1 in order is the same as W calls of `read`; the
-        caller owns that order (self.n is not touched)."""
-        o = self.o if out is None else out
+        caller owns that order (self.n is not touched).  The call keeps q's
+        address, so a q that read() would copy is refused."""
+        if self._query(q) is not q:
+            raise ValueError(f"q must be a contiguous {self._io} tensor [B][H][K] on {self.S.device}")
+        o = self._output(out)
         st = self.stream()
         if n == self.window - 1:
             return B.prepare_update(self.cfg, self.S, self.omega, self.ring, n, q, self.U, o, st, cmap=self.cmap)
@@ -162,14 +166,36 @@ class SketchSSMLayer:
         return cls.write_token is _WRITE and cls.read is _READ and "write_token" not in own and "read" not in own
 
     def _as_they_are(self, inp: dict) -> bool:
-        """Whether the token's tensors are laid out as the kernels read them
+        """Whether the token's update inputs are laid out as the kernels read them
         (dtype, shape, contiguous, this device, 16-byte aligned)."""
         for name, dtype, shape in self._token_like:
             t = inp[name]
-            if (t.dtype is not dtype or t.shape != shape or not t.is_contiguous() or t.device != self.S.device
+            if (t.dtype is not dtype or t.shape != shape or not t.is_contiguous() or t.get_device() != self._index
                     or t.data_ptr() & 15):
                 return False
         return True
+
+    def _query(self, q):
+        """q as the kernels read it: itself where it is [B][H][K] in the io dtype
+        on this device, contiguous (whatever its shape), else a copy (an int is
+        an address)."""
+        if isinstance(q, torch.Tensor) and (
+                q.dtype is not self._io or not q.is_contiguous() or q.get_device() != self._index
+                or q.numel() < self.batch * self.heads * self.dk):
+            return torch.empty((self.batch, self.heads, self.dk), dtype=self._io, device=self.S.device).copy_(q)
+        return q
+
+    def _output(self, out):
+        """The tensor o is written to: the layer's own, or `out`, which must be
+        able to hold it (a view cannot be copied back into)."""
+        if out is None:
+            return self.o
+        if isinstance(out, torch.Tensor) and (
+                out.dtype is not torch.float32 or not out.is_contiguous()
+                or out.numel() < self.batch * self.heads * self.dv
+                or (out.get_device() != self._index and not out.is_pinned())):
+            raise ValueError(f"out must be a contiguous fp32 tensor [B][H][V] on {self.S.device}")
+        return out
 
     def step(self, inp: dict, out: torch.Tensor | None = None) -> torch.Tensor:
         """write_token + read.  Where the token's tensors can be read as they
@@ -182,10 +208,10 @@ class SketchSSMLayer:
         if not (self._own_calls() and self._as_they_are(inp)):
             self.write_token(inp)
             return self.read(inp["q"], out)
-        o = self.o if out is None else out
+        q, o = self._query(inp["q"]), self._output(out)
         n = self.n
         B.sketchssm_step(self.cfg, self.baseline, self.S, self.omega, self.coef, self.ring, n, inp["k"], inp["v"],
-                         inp["beta"], inp["log_decay"], inp["q"], self.U, o, self.stream(), cmap=self.cmap)
+                         inp["beta"], inp["log_decay"], q, self.U, o, self.stream(), cmap=self.cmap)
         self.n = 0 if n == self.window - 1 else n + 1
         return o
 

@@ -70,7 +70,7 @@ def test_step_is_the_append_and_the_read(case, monkeypatch):
 
 
 def test_tensors_the_kernels_cannot_read_are_copied(monkeypatch):
-    """A strided key, a half-precision value, a broadcast gate, a misaligned
+    """A strided key, an fp32 value in a bf16 layer, a broadcast gate, a misaligned
     decay and a subclass with its own append: the same results through the slot."""
     class Own(SketchSSMLayer):
         appended = 0
@@ -173,3 +173,36 @@ def test_a_replaced_append_or_read_is_called(where, name, monkeypatch):
     assert calls == [name]
     monkeypatch.undo()
     assert torch.equal(a, two.step(inp))
+
+
+def test_a_query_the_kernels_cannot_read_is_copied_and_such_an_output_refused():
+    """A strided, another-dtype, host or broadcast q gives what its plain copy
+    gives, through step() and read(); prepared_read(), which keeps the address,
+    refuses it, and every call an output it cannot write as [B][H][V]."""
+    wl, (one, two) = _pair("gdn", 128, 128, 16, 4, "bf16", "f32", 0, False, None)
+    for t in range(8):
+        inp = inputs.step_inputs(wl, t, "cuda")
+        plain = dict(inp)
+        wide = torch.empty((3, 3, 256), dtype=torch.bfloat16, device="cuda")
+        wide[..., ::2] = inp["q"]
+        if t % 4 == 3:
+            inp["q"] = inp["q"][:1, :1]
+            plain["q"] = inp["q"].expand(3, 3, 128).contiguous()
+        q = (wide[..., ::2], inp["q"].float(), inp["q"].cpu(), inp["q"])[t % 4]
+        with pytest.raises(ValueError):
+            one.prepared_read(q, 0)
+        if t < 4:
+            a = one.step(dict(inp, q=q)).clone()
+        else:
+            one.write_token(inp)
+            a = one.read(q).clone()
+        assert torch.equal(a, two.step(plain)), t
+    for out in (torch.empty((3, 3, 256), device="cuda")[..., ::2], torch.empty((3, 3, 128), device="cuda").bfloat16(),
+                torch.empty((3, 3, 64), device="cuda"), torch.empty((3, 3, 128))):
+        for call in (lambda: one.step(plain, out), lambda: one.read(plain["q"], out),
+                     lambda: one.prepared_read(plain["q"], 0, out)):
+            with pytest.raises(ValueError):
+                call()
+    assert one.n == 0
+    flat = torch.empty(3 * 3 * 128, device="cuda")  # contiguous in another shape: as it is
+    assert torch.equal(one.step(dict(plain, q=plain["q"].view(9, 128)), flat).view(3, 3, 128), two.step(plain))

@@ -56,6 +56,14 @@ __device__ __forceinline__ floatx4 lds4(const float* p) {
 // different banks without padding.
 template <int K> __device__ __forceinline__ int om_at(int j, int k) { return j * K + (k ^ ((j & 7) << 2)); }
 
+// Element e of a head's Omega in global memory: uniform base and 32-bit byte
+// offset.  With 64-bit lane addresses, and the next tile's loads held back by
+// the branch of a rank check, the full-rank initial sketch took a third longer
+// (GDN K = 128, V = 64, 1 GiB of state, fp32 sketch: 1,143 -> 775 us).
+__device__ __forceinline__ float om_ld(const float* om, uint32_t e) {
+  return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(om) + 4 * e);
+}
+
 // Sixteen 4 x 4 x 1 products at once, block b on lanes 4 b .. 4 b + 3:
 // c[i] of lane j += (a of lane i) (b of lane j), i and j within the quad.
 __device__ __forceinline__ floatx4 mfma4x4(float a, float b, floatx4 c) {
@@ -1020,7 +1028,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
             w = lds4(&OmL[om_at<K>(jj, 16 * kt + 4 * lg)]);
           } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) w[i] = (jj < R) ? om[(16 * kt + 4 * lg + i) * R + jj] : 0.f;
+            for (int i = 0; i < 4; ++i) w[i] = om_ld(om, (uint32_t)((16 * kt + 4 * lg + i) * R + jj));
           }
 #pragma unroll
           for (int i = 0; i < 4; ++i)
@@ -1067,10 +1075,11 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
           }
           // columns 16 jt + 4 lg .. +3 of value v; panels of 16 bytes per value:
           // fp32 U[B][H][R/4][V][4], bf16 U[B][H][R/8][V][8]
-          // (panels past this head's rank are not stored; the tail of its last
-          // panel holds zeros)
           constexpr int PWU = 16 / (int)sizeof(SK);
-          if (16 * jt + 4 * lg < R && ((16 * jt + 4 * lg) / PWU) * PWU < rh) {
+          // panels past this head's rank are not stored; the tail of its last panel
+          // holds zeros (the full rank has no table: without the branch the next
+          // tile's Omega is read ahead of these stores)
+          if (!OM_LDS || (16 * jt + 4 * lg < R && ((16 * jt + 4 * lg) / PWU) * PWU < rh)) {
             SK* Ui = static_cast<SK*>(a.U) + item * (size_t)V * R;
             if constexpr (sizeof(SK) == 4) {
               reinterpret_cast<float4*>(Ui)[(4 * jt + lg) * V + v] = make_float4(acc[0], acc[1], acc[2], acc[3]);

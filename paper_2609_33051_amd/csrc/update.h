@@ -649,6 +649,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
 
   // ---- every small load first (window, query, rows of T^{-1}, Omega), then the
   // state: the staged values reach LDS while the state read is still in flight
+  // (STATE_LATE: before it is issued)
   float egn = 1.f;  // the chunk's e^{g_n} (scalar decay)
   floatx4 tu = {0.f, 0.f, 0.f, 0.f};  // this lane's entries of T^{-1} Diag(beta): row lr, columns 4 lg .. (erase families)
   Raw<IO, 1> qr;  // this thread's query channel, raw (converted at the staging, so no wait here)
@@ -663,9 +664,9 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
   // after the channel work: 436, 462).  The others issue it with the staging's
   // loads, unconditionally, so that waiting for the staged values never waits
   // for it: Mamba-2's 32 KB (397 us either way), windows of two chunks (284
-  // against 295) and the flushes that build a map, which are not bound by the
-  // stream (GDN 492 against 507).
-  constexpr bool STATE_LATE = ERASE && CH == 1 && P == 0;
+  // against 295), the flushes that build a map, which are not bound by the
+  // stream (GDN 492 against 507), and the full rank's, bound by Omega's reads.
+  constexpr bool STATE_LATE = ERASE && CH == 1 && P == 0 && R <= 32;
   static_assert(VT % 4 == 0, "every wave owns the same number of value tiles");
   auto load_state = [&]() {
 #pragma unroll
@@ -679,6 +680,41 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
       }
     }
   };
+  auto load_omega = [&]() {
+#pragma unroll
+    for (int c = 0; c < OQ; ++c) {
+      const int i = tid + 256 * c;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) omv[c].e[e] = 0.f;
+      if (i < K * R / 4 && 4 * (i % (R / 4)) < rh) omv[c].load(a.omega + (size_t)h * K * R + 4 * i);
+    }
+  };
+  auto stage_omega = [&]() {
+#pragma unroll
+    for (int c = 0; c < OQ; ++c) {
+      const int i = tid + 256 * c;
+      if (i < K * R / 4) {
+        Vec<4> w = omv[c];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (4 * (i % (R / 4)) + e >= rh) w.e[e] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) OmL[om_at<K>(4 * (i % (R / 4)) + e, i / (R / 4))] = w.e[e];
+      }
+    }
+    if constexpr (R < 16 * RT) {  // zero columns R..16 RT-1
+      for (int i = tid; i < (16 * RT - R) * K / 4; i += 256)
+        *reinterpret_cast<float4*>(&OmL[R * K + 4 * i]) = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  };
+  if (STATE_LATE && !flush) {
+    // the initial sketch has nothing to hide the state's latency behind but
+    // Omega's: its loads on a path of their own, where no wait covers both
+    if constexpr (OM_LDS) load_omega();
+    load_state();
+    compiler_fence();
+    if constexpr (OM_LDS) stage_omega();
+  }
 #pragma unroll
   for (int ch = 0; ch < CH; ++ch) {
     const int sb = 16 * ch;                                 // the chunk's first slot in the ring
@@ -734,15 +770,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
       }
     }
     if constexpr (OM_LDS) {
-      if (ch == 0 && want_U) {
-#pragma unroll
-        for (int c = 0; c < OQ; ++c) {
-          const int i = tid + 256 * c;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) omv[c].e[e] = 0.f;
-          if (i < K * R / 4 && 4 * (i % (R / 4)) < rh) omv[c].load(a.omega + (size_t)h * K * R + 4 * i);
-        }
-      }
+      if (ch == 0 && want_U && (flush || !STATE_LATE)) load_omega();
     }
 
     if (!STATE_LATE && ch == 0) load_state();
@@ -750,24 +778,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
 
     // ---- staged values into LDS
     if constexpr (OM_LDS) {
-      if (ch == 0 && want_U) {
-#pragma unroll
-        for (int c = 0; c < OQ; ++c) {
-          const int i = tid + 256 * c;
-          if (i < K * R / 4) {
-            Vec<4> w = omv[c];
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (4 * (i % (R / 4)) + e >= rh) w.e[e] = 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) OmL[om_at<K>(4 * (i % (R / 4)) + e, i / (R / 4))] = w.e[e];
-          }
-        }
-        if constexpr (R < 16 * RT) {  // zero columns R..16 RT-1
-          for (int i = tid; i < (16 * RT - R) * K / 4; i += 256)
-            *reinterpret_cast<float4*>(&OmL[R * K + 4 * i]) = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-      }
+      if (ch == 0 && want_U && (flush || !STATE_LATE)) stage_omega();
     }
     if (flush) {
 #pragma unroll
@@ -849,7 +860,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
       }
     }
     lds_barrier();
-    if constexpr (STATE_LATE) {
+    if (STATE_LATE && flush) {
       load_state();
       compiler_fence();
     }

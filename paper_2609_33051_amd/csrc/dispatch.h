@@ -50,6 +50,17 @@ constexpr int flush_cap(int kind, int K, int V) {
   if (kind != MAMBA2) return kb >= 64 ? 3 : 0;
   return kb >= 64 ? 2 : kb >= 32 ? 3 : 5;
 }
+// The map flushes keep their occupancy but for Mamba-2's 32 KB items at rank 8
+// with fp32 inputs, W <= 16: six of those (with 12 KB of inputs each and the
+// least arithmetic) run slower than five (us at six / five, 1 GiB of state,
+// fp32 / bf16 sketch: P = 4 509, 479 / 495, 470; exact 502, 470 / 485, 465;
+// bf16 inputs P = 4 447, 435 / 454, 453; rank 16 exact, fp32 inputs 554, 518 /
+// 562, 553).
+template <int KIND, int K, int V, int R, int WM, typename IO, int P>
+constexpr int flush_cap_of() {
+  if (P == 0) return flush_cap(KIND, K, V);
+  return KIND == MAMBA2 && 4 * K * V == 32 * 1024 && R == 8 && WM == 16 && sizeof(IO) == 4 ? 5 : 0;
+}
 // Bytes of state in flight per CU of the single-token update, whose workgroups
 // are one 16-value tile each (us at four / five / six / eight tiles of 8 KB and
 // uncapped, 1 GiB of state: GDN K = V = 128 332 / 322 / 329 / 346 / 353, Mamba-2
@@ -90,7 +101,7 @@ int launch_full_read(const DecodeArgs& a, hipStream_t s) {
 template <int KIND, int K, int V, int R, int WM, typename IO, typename SK, int P>
 int launch_update(const UpdateArgs& a, hipStream_t s) {
   const size_t items = (size_t)a.B * a.H;
-  constexpr int kCap = P == 0 ? flush_cap(KIND, K, V) : 0;
+  constexpr int kCap = flush_cap_of<KIND, K, V, R, WM, IO, P>();
   static const size_t cap = kCap ? lds_for_cap(&update_kernel<KIND, K, V, R, WM, IO, SK, P>, kCap) : 0;
   hipLaunchKernelGGL((update_kernel<KIND, K, V, R, WM, IO, SK, P>), dim3((unsigned)items), dim3(256), a.nt > 0 ? cap : 0,
                      s, a);

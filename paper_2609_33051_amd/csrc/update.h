@@ -1117,10 +1117,15 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
             wave_lds_sync();
 #pragma unroll
             for (int st = 0; st < 4; ++st) nacc[kt] = mfma4(aop[t][st], cx[(4 * st + lg) * XP + lr], nacc[kt]);
-            // one accumulation per element (a four-term sum here keeps the scaled
-            // values live across the syncs: 22 more registers for Mamba-2)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) msq += (xs[t][kt][i] * msc) * (xs[t][kt][i] * msc);
+            // summed here and now: left to the compiler, the whole chain sinks below
+            // the last block and holds every scaled value till then (81 to 83
+            // registers for Mamba-2's exact map at V = 64, 168 for its P = 4 map at
+            // K = V = 128, r = 32)
+            msq += xsc.x * xsc.x;
+            msq += xsc.y * xsc.y;
+            msq += xsc.z * xsc.z;
+            msq += xsc.w * xsc.w;
+            asm volatile("" : "+v"(msq));
           }
         }
       }

@@ -668,6 +668,15 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
   // stream (GDN 492 against 507), and the full rank's, bound by Omega's reads.
   constexpr bool STATE_LATE = ERASE && CH == 1 && P == 0 && R <= 32;
   static_assert(VT % 4 == 0, "every wave owns the same number of value tiles");
+  // A token of its own arrays (sketchssm_step): one load from a base chosen per
+  // lane needs 64-bit lane addresses, whether or not the call was given a token
+  // (64 MiB of state, Mamba-2 K = 128, V = 64, r = 16: 27.4 us against 26.8 with
+  // the token loaded apart, r = 8 27.3 against 26.1).  Where the loads take more
+  // registers the branch costs more: fp32 inputs (K = V = 128, W = 32, 1 GiB 447
+  // against 489), V = 128 (64 MiB, rank 0: 24.0 against 25.5) and the erase
+  // families' two chunks (GDN 39.4 against 41.1, KDA 42.9 against 44.3; one chunk
+  // the same).
+  constexpr bool APART = !ERASE && sizeof(IO) == 2 && V == 64;
   auto load_state = [&]() {
 #pragma unroll
     for (int t = 0; t < VTW; ++t) {
@@ -726,6 +735,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
     // to the ring below) when the call was given them
     const bool own = last && a.tk != nullptr;
     float bl = 0.f, ll = 0.f;             // wave 0, lane s: beta_s and (scalar decay) log alpha_s
+    float bt = 0.f, lt = 0.f;             // the token's own (uniform)
     float gk[CHAN ? SP : 1];              // KDA: g_s of channel tid % K
     Raw<IO, KPL> kr[NG / 4];              // ring keys, row layout (slot 4 (wave + 4 gq) + row)
     Raw<IO, VR> vr[NG / 4];               // raw values
@@ -734,12 +744,17 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
     if (flush) {
       // per-slot scalars: lane s of wave 0 loads slot s; every slot load is
       // issued before any is used (slots past n re-read slot n, in bounds, and
-      // are masked afterwards), so no load waits on a branch
+      // are masked afterwards), so no load waits on a branch.  APART: ring and
+      // token are loaded by loads of their own, each from a uniform base
       if (tid < SP) {
-        const bool tok = own && tid >= n;
+        const bool tok = !APART && own && tid >= n;
         const size_t si = tok ? item : item * W + sb + (tid < n ? tid : n);
         bl = (tok ? a.tbeta : a.rbeta)[si];
         if constexpr (!CHAN) ll = (tok ? a.tla : a.rla)[si];
+      }
+      if (APART && own) {
+        bt = a.tbeta[item];
+        if constexpr (!CHAN) lt = a.tla[item];
       }
       if constexpr (CHAN) {
         const float* lcur = own ? a.tla + item * K : a.rla + (item * W + sb + n) * K;
@@ -751,9 +766,13 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
         const int s = 4 * (wave + 4 * gq) + row;
         const size_t si = item * W + sb + s;
         if (s <= n) {
-          const bool tok = own && s == n;
+          const bool tok = !APART && own && s == n;
           kr[gq].load((tok ? static_cast<const IO*>(a.tk) + item * K : static_cast<const IO*>(a.rk) + si * K) + col * KPL);
           vr[gq].load((tok ? static_cast<const IO*>(a.tv) + item * V : static_cast<const IO*>(a.rv) + si * V) + col * VR);
+        }
+        if (APART && own && s == n) {
+          kr[gq].load(static_cast<const IO*>(a.tk) + item * K + col * KPL);
+          vr[gq].load(static_cast<const IO*>(a.tv) + item * V + col * VR);
         }
       }
       if constexpr (ERASE && !CHAN)
@@ -819,8 +838,8 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
           }
         }
         if (tid == n) {
-          const_cast<float*>(a.rbeta)[cur] = bl;
-          if constexpr (!CHAN) const_cast<float*>(a.rla)[cur] = ll;
+          const_cast<float*>(a.rbeta)[cur] = APART ? bt : bl;
+          if constexpr (!CHAN) const_cast<float*>(a.rla)[cur] = APART ? lt : ll;
         }
         if constexpr (CHAN) {
           if (tid < K) const_cast<float*>(a.rla)[cur * K + tid] = gk[SP - 1];  // every slot from n on holds log alpha_n
@@ -832,6 +851,10 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
         // lanes) and c_s = e^{g_n - g_s}, slots past n zero
         const int sl = tid;
         const bool live = sl <= n && sl < SP;
+        if (APART && own && sl == n) {
+          bl = bt;
+          ll = lt;
+        }
         float g = (!CHAN && live) ? ll : 0.f;
 #pragma unroll
         for (int d = 1; d < SP; d <<= 1) {

@@ -41,26 +41,29 @@ size_t lds_for_cap(Kernel kern, int cap) {
 //   GDN      16 KB  672 / 559 / 497 / 470 / 450     -> none
 //            32 KB  575 / 489 / 440 / - / 436       -> none
 //            64 KB  456 / 432 / - / - / 421..452    -> 3  (KDA 470 / 446 / - / - / 477)
+// (rank 16, W = 16, bf16 inputs).  Wider inputs or a larger rank move it (us at
+// the cap above / at the one taken, 1 GiB of state): Mamba-2 16 KB fp32 inputs rank 0 428 / 417,
+// rank 16, W = 32 577 / 563; 32 KB rank 32, W = 16, bf16 437 / 418; 64 KB rank
+// 32, W = 32, bf16 478 / 441.
 // The flushes that build a state-dependent map and the decode do arithmetic or
 // wait on latency between their loads and keep their occupancy (capping them
 // measured slower), as does the initial sketch (a read of the state, run once
-// after prefill).
-constexpr int flush_cap(int kind, int K, int V) {
-  const int kb = 4 * K * V / 1024;
-  if (kind != MAMBA2) return kb >= 64 ? 3 : 0;
-  return kb >= 64 ? 2 : kb >= 32 ? 3 : 5;
-}
-// The map flushes keep their occupancy but for Mamba-2's 32 KB items at rank 8
-// with fp32 inputs, W <= 16: six of those (with 12 KB of inputs each and the
-// least arithmetic) run slower than five (us at six / five, 1 GiB of state,
-// fp32 / bf16 sketch: P = 4 509, 479 / 495, 470; exact 502, 470 / 485, 465;
-// bf16 inputs P = 4 447, 435 / 454, 453; rank 16 exact, fp32 inputs 554, 518 /
-// 562, 553).
+// after prefill); but for Mamba-2's 32 KB items at rank 8 with fp32 inputs,
+// W <= 16: six of those (with 12 KB of inputs each and the least arithmetic) run
+// slower than five (us at six / five, 1 GiB of state, fp32 / bf16 sketch: P = 4
+// 509, 479 / 495, 470; exact 502, 470 / 485, 465; bf16 inputs P = 4 447, 435 /
+// 454, 453; rank 16 exact, fp32 inputs 554, 518 / 562, 553).
 template <int KIND, int K, int V, int R, int WM, typename IO, int P>
-constexpr int flush_cap_of() {
-  if (P == 0) return flush_cap(KIND, K, V);
-  return KIND == MAMBA2 && 4 * K * V == 32 * 1024 && R == 8 && WM == 16 && sizeof(IO) == 4 ? 5 : 0;
+constexpr int flush_cap() {
+  constexpr int kb = 4 * K * V / 1024;
+  constexpr bool narrow = sizeof(IO) == 2;
+  if (P != 0) return KIND == MAMBA2 && kb == 32 && R == 8 && WM == 16 && !narrow ? 5 : 0;
+  if (KIND != MAMBA2) return kb >= 64 ? 3 : 0;
+  if (kb >= 64) return R == 32 && WM == 32 && narrow ? 3 : 2;
+  if (kb >= 32) return R == 32 && WM == 16 && narrow ? 4 : 3;
+  return narrow || R >= 32 ? 5 : R > 0 ? 4 : 3;
 }
+
 // Bytes of state in flight per CU of the single-token update, whose workgroups
 // are one 16-value tile each (us at four / five / six / eight tiles of 8 KB and
 // uncapped, 1 GiB of state: GDN K = V = 128 332 / 322 / 329 / 346 / 353, Mamba-2
@@ -101,7 +104,7 @@ int launch_full_read(const DecodeArgs& a, hipStream_t s) {
 template <int KIND, int K, int V, int R, int WM, typename IO, typename SK, int P>
 int launch_update(const UpdateArgs& a, hipStream_t s) {
   const size_t items = (size_t)a.B * a.H;
-  constexpr int kCap = flush_cap_of<KIND, K, V, R, WM, IO, P>();
+  constexpr int kCap = flush_cap<KIND, K, V, R, WM, IO, P>();
   static const size_t cap = kCap ? lds_for_cap(&update_kernel<KIND, K, V, R, WM, IO, SK, P>, kCap) : 0;
   hipLaunchKernelGGL((update_kernel<KIND, K, V, R, WM, IO, SK, P>), dim3((unsigned)items), dim3(256), a.nt > 0 ? cap : 0,
                      s, a);

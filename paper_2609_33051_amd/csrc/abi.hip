@@ -183,15 +183,7 @@ skssm::DecodeArgs decode_args(const skssm_config* c, const skssm_ring* r, int32_
     a.cv = t->v;
     a.cbeta = t->beta;
     a.cla = t->log_decay;
-    a.cs = 1;
     a.append = 1;
-  } else {  // slot n of the ring
-    const size_t io = c->io_dtype == SKSSM_BF16 ? 2 : 4;
-    a.ck = static_cast<const char*>(r->k) + (size_t)n * c->dk * io;
-    a.cv = static_cast<const char*>(r->v) + (size_t)n * c->dv * io;
-    a.cbeta = r->beta + n;
-    a.cla = r->log_decay + (size_t)n * (c->kind == SKSSM_KDA ? c->dk : 1);
-    a.cs = c->window;
   }
   a.o = o;
   return a;

@@ -24,28 +24,24 @@ struct DecodeArgs {
   int B, H, W, n;                 // batch, heads, window, slot of the current token
   int ragged;                     // hrank holds the per-head ranks
   int ndense;                     // dense-fallback heads (ragged)
-  int cs;                         // row stride of the current token's inputs (ck ..)
-  int append;                     // the token comes from its own arrays
+  int append;                     // the token comes from its own arrays (ck ..) and goes into slot n
   const void* q;                  // [B][H][K] io, current query
-  // the current token's raw inputs: row i * cs of these is item i's (ring slot
-  // n: offset to it, cs = W; or the token's own arrays [B][H][..], cs = 1,
-  // which this call appends to the slot)
-  const void* ck;                 // rows of K io
-  const void* cv;                 // rows of V io
-  const float* cbeta;             // rows of 1
-  const float* cla;               // rows of 1 or K
-  const void* rk;                 // ring [B][H][W][K] io      raw keys
-  const void* rv;                 // ring [B][H][W][V] io      raw values
-  const float* rbeta;             // ring [B][H][W]            write gates
-  const float* rla;               // ring [B][H][W] or [..][K] log decays
   const void* U;                  // [B][H][R/P][V][P], P = 4 (fp32) or 8 (bf16)  (sketch read)
   const float* coef;              // [H][R][K]           (sketch read, offline map; NULL with a state-dependent map)
   const void* cmap;               // [B][H][K/CPW][R][CPW] state-dependent map, sketch dtype, CPW = 16 B / element (or NULL)
   const float* S;                 // [B][H][V][K]        (exact baseline)
+  const void* rk;                 // ring [B][H][W][K] io      raw keys
+  const void* rv;                 // ring [B][H][W][V] io      raw values
+  const float* rbeta;             // ring [B][H][W]            write gates
+  const float* rla;               // ring [B][H][W] or [..][K] log decays
   void* rf;                       // ring [W][H][B][R]  projected erase factors, sketch dtype (GDN/KDA sketch read)
   float* rpi;                     // ring [W][H][B][K]  erase factors (GDN/KDA baseline)
   float* rt;                      // ring [W][H][B][W]  rows of T^{-1} (GDN/KDA)
   float* o;                       // [B][H][V]
+  const void* ck;                 // append: the current token's own arrays, [B][H][K] io
+  const void* cv;                 // [B][H][V] io
+  const float* cbeta;             // [B][H]
+  const float* cla;               // [B][H] or [..][K]
   alignas(4) uint8_t hrank[kMaxRaggedHeads];
   alignas(4) uint8_t hlist[kMaxRaggedHeads];  // heads in launch order: the dense ones first (ragged)
 };

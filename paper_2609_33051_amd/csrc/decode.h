@@ -64,6 +64,13 @@ struct RowLoads {
   // item contiguous; slot s of a derived field (f, pi, rows of T^{-1}) at
   // field + (s * B*H + dp) * w with dp = h * B + b: one slot of all items
   // contiguous, head-major within the slot.
+  //
+  // APPEND: the current token comes from its own arrays instead of slot n.  A
+  // compile-time choice: one set of pointers with a run-time stride for both took
+  // four to ten registers more in the plain reads, past a wave's line for GDN and
+  // KDA at K = V = 64 (KDA, rank 32, W = 32, P = 4, fp32 sketch, slot 16, 65,536
+  // items 320 -> 341 us).
+  template <bool APPEND>
   __device__ __forceinline__ void load(const DecodeArgs& a, size_t item, size_t dp, int row, int col) {
     const int n = a.n;
     const size_t W = (size_t)a.W, NI = (size_t)a.B * a.H;
@@ -85,18 +92,19 @@ struct RowLoads {
       }
     }
     const uint32_t koff = (uint32_t)(col * KPL), voff = (uint32_t)(col * VR);
-    const size_t cur = item * (size_t)a.cs;          // the current token's row
+    const size_t cur = APPEND ? item : item * W + n;  // the current token's row
+    const float* la_p = APPEND ? a.cla : a.rla;
     q_raw.load_nt(static_cast<const IO*>(a.q) + item * K + koff);
-    k_raw.load_nt(static_cast<const IO*>(a.ck) + cur * K + koff);
-    v_raw.load_nt(static_cast<const IO*>(a.cv) + cur * V + voff);
-    beta_t = a.cbeta[cur];
+    k_raw.load_nt(static_cast<const IO*>(APPEND ? a.ck : a.rk) + cur * K + koff);
+    v_raw.load_nt(static_cast<const IO*>(APPEND ? a.cv : a.rv) + cur * V + voff);
+    beta_t = (APPEND ? a.cbeta : a.rbeta)[cur];
     if constexpr (CHAN) {
       Vec<KPL> t;
-      t.load_nt(a.cla + cur * K + koff);
+      t.load_nt(la_p + cur * K + koff);
 #pragma unroll
       for (int m = 0; m < KPL; ++m) la[m] = t.e[m];
     } else {
-      la[0] = a.cla[cur];
+      la[0] = la_p[cur];
     }
 #pragma unroll
     for (int m = 0; m < GD; ++m) gprev[m] = 0.f;
@@ -354,7 +362,7 @@ __device__ __forceinline__ void full_read_item(const DecodeArgs& a, size_t item,
   const uint32_t koff = (uint32_t)(col * KPL);
 
   L r;
-  r.load(a, item, dp, row, col);
+  r.template load<APPEND>(a, item, dp, row, col);
   float ps[ERASE ? NG : 1][KPL];     // ring pi of slot 4 gi + row (row layout)
   if constexpr (ERASE) {
     // slot clamped below n and the value selected (no guarded load)
@@ -589,7 +597,7 @@ __global__ __launch_bounds__(256) void decode_kernel(const DecodeArgs a) {
   // flight, which serialises the item's memory accesses.  The raw ring slots
   // are guarded per lane (slot 4 gi + row < n), which masks lanes instead.
   L r;
-  r.load(a, item, dp, row, col);
+  r.template load<APPEND>(a, item, dp, row, col);
   float fs[ERASE ? NG : 1][RP];      // ring f of slot 4 gi + row, component col + 16 p
   Raw<SK, PW> Ur[VPL][UP];           // sketch panels (value layout), loaded after the slot dot products
   // the item's state-dependent map (P != 0): this lane's channels of its rows

@@ -805,7 +805,7 @@ __global__ __launch_bounds__(256) void full_read_kernel(const DecodeArgs a) {
   const uint32_t lwg = (G % 8 == 0) ? (wg % 8) * (G / 8) + wg / 8 : wg;
   const size_t item = (size_t)lwg * 4 + wave;
   if (item >= NI) return;  // wave-uniform; no block barrier in this kernel
-  const uint32_t b = (uint32_t)item / (uint32_t)a.H, h = (uint32_t)item - b * (uint32_t)a.H;  // B*H <= 2^30
+  const uint32_t b = (uint32_t)item / (uint32_t)a.H, h = (uint32_t)item - b * (uint32_t)a.H;  // B*H < 2^23
   full_read_item<KIND, K, V, WMAX, IO, APPEND>(a, item, (size_t)h * a.B + b, lane, wscr + wave * WS);
 }
 

@@ -47,23 +47,6 @@ __device__ __forceinline__ uint32_t ld_nt(const uint32_t* p) { return __builtin_
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// One io element kept in a full 32-bit register (raw bits, zero-extended for
-// bf16): loads need no packing into register halves, so the compiler does not
-// have to wait for them early.
-template <typename IO> __device__ __forceinline__ uint32_t ld_bits(const IO* p, uint32_t off);
-template <> __device__ __forceinline__ uint32_t ld_bits<float>(const float* p, uint32_t off) {
-  return __float_as_uint(p[off]);
-}
-template <> __device__ __forceinline__ uint32_t ld_bits<bf16_t>(const bf16_t* p, uint32_t off) {
-  return (uint32_t)p[off];
-}
-template <typename IO> __device__ __forceinline__ void st_bits(IO* p, uint32_t off, uint32_t x);
-template <> __device__ __forceinline__ void st_bits<float>(float* p, uint32_t off, uint32_t x) {
-  p[off] = __uint_as_float(x);
-}
-template <> __device__ __forceinline__ void st_bits<bf16_t>(bf16_t* p, uint32_t off, uint32_t x) {
-  p[off] = (bf16_t)x;
-}
 // fp32 -> bf16 bits, round to nearest with ties to even (v_cvt_pk_bf16_f32):
 // two values, the first in the low half, or one.  The same rounding in integer
 // arithmetic takes seven instructions a value; the flush that builds a rank-32
@@ -90,11 +73,6 @@ template <> __device__ __forceinline__ void st_elem4<float>(float* p, float a, f
 }
 template <> __device__ __forceinline__ void st_elem4<bf16_t>(bf16_t* p, float a, float b, float c, float d) {
   *reinterpret_cast<uint2*>(p) = make_uint2(bf16_pack2(a, b), bf16_pack2(c, d));
-}
-
-template <typename IO> __device__ __forceinline__ float bits_f32(uint32_t x) {
-  if constexpr (sizeof(IO) == 2) return bf16_lo(x);
-  else return __uint_as_float(x);
 }
 
 // N raw elements of the io dtype, moved with the widest aligned accesses.
@@ -249,13 +227,6 @@ __device__ __forceinline__ float row_sum16(float x) {
   x += dpp<0x4E>(x);   // quad_perm [2,3,0,1]
   x += dpp<0x141>(x);  // row_half_mirror
   x += dpp<0x140>(x);  // row_mirror
-  return x;
-}
-
-// Sum over a quad of lanes (lane & ~3 .. lane | 3).
-__device__ __forceinline__ float quad_sum(float x) {
-  x += dpp<0xB1>(x);  // quad_perm [1,0,3,2]
-  x += dpp<0x4E>(x);  // quad_perm [2,3,0,1]
   return x;
 }
 

@@ -99,11 +99,13 @@ template <int K, int R, int P, int MT, int RT, int LSZ, int USZ, typename SK>
 __device__ __forceinline__ void coef_map_tail(const UpdateArgs& a, size_t item, int wave, int lane, int tid, int rh,
                                               const floatx4 (&nacc)[MT], const floatx4 (&gram)[RT],
                                               const float (&dsq)[RT], float msq,
-                                              float* Ls, float* Us, float* cmS, const float* OmL, float* Fext) {
-  static_assert(LSZ >= 4 * K * P && USZ >= 4 * R * 5, "staging buffers too small for the map's partial sums");
+                                              float* Ls, float* Us, float* cmS, const float* OmL) {
   static_assert(MT % 4 == 0, "the four waves split the k tiles evenly");
   constexpr int FBP = P + 1;                           // row pitch of F1 (odd: lanes of a read spread over banks)
-  constexpr bool FB_ALIAS = LSZ >= P * K + 16 * RT * FBP;
+  // in Ls: the waves' N rows (4 K P words), then in their place M'^T and F1, and
+  // past them L_G and w
+  static_assert(LSZ >= 4 * K * P + 5 * R && 4 * K * P >= P * K + 16 * RT * FBP && USZ >= 4 * R * 5,
+                "staging buffers too small for the map's partial sums");
   const int lr = lane & 15, lg = lane >> 4;
   // the squared sketch columns summed over the four lane rows (the Gram
   // products already summed over this wave's values)
@@ -114,9 +116,7 @@ __device__ __forceinline__ void coef_map_tail(const UpdateArgs& a, size_t item, 
   lds_barrier();  // every wave is done with the window staging (Ls, Us), reused below
   float* cmN = Ls;  // [wave][K][P]
   float* cmG = Us;  // [wave][R][5]
-  // [R][P] -w L_G, then [R] w = D^{-1} d: behind the waves' N rows, or behind
-  // R^{-1} where those leave no room
-  float* sL = LSZ >= 4 * K * P + 5 * R ? Ls + 4 * K * P : cmS + 8 + 16;
+  float* sL = Ls + 4 * K * P;  // [R][P] -w L_G, then [R] w = D^{-1} d
   if (lg == 0) {
 #pragma unroll
     for (int kt = 0; kt < MT; ++kt)
@@ -285,7 +285,7 @@ __device__ __forceinline__ void coef_map_tail(const UpdateArgs& a, size_t item, 
   }
   lds_barrier();  // the waves' N rows are consumed: M'^T and F1 take their place
   float* Mb = Ls;                              // [K][P]   M'^T
-  float* Fb = FB_ALIAS ? Ls + P * K : Fext;    // [16 RT][FBP]  row j = F1 row j, zero past R
+  float* Fb = Ls + P * K;                      // [16 RT][FBP]  row j = F1 row j, zero past R
   if (tid < K) *reinterpret_cast<float4*>(&Mb[tid * P]) = make_float4(Mk[0], Mk[1], Mk[2], Mk[3]);
   if (wave == 0 && lane < 16 * RT) {
     float* fr = Fb + lane * FBP;
@@ -589,7 +589,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
   const int lr = lane & 15, lg = lane >> 4;   // MFMA lane coordinates
   const int row = lg, col = lr;               // row-layout coordinates (same lanes)
   const int H = a.H, W = a.W, nw = a.n;  // nw: the window's current slot
-  const size_t item = blockIdx.x;  // b * H + h (B*H <= 2^30)
+  const size_t item = blockIdx.x;  // b * H + h (B*H < 2^23)
   const int h = (int)(blockIdx.x % (uint32_t)H);
   const bool flush = a.nt > 0;
   // slot s of an item: raw ring fields at (item * W + s) * width, derived
@@ -615,19 +615,15 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
   static_assert(P == 0 || (P == 4 && R >= 8 && R <= 32) || (EXACT && R >= 8 && R <= 16),
                 "state-dependent maps: P = 4 with rank 8..32, or the exact metric with rank 8..16");
   constexpr int XP = 20;                                        // row pitch of a transposed 16 x 16 block
-  // When the key staging Ls has room, that scratch lives in Ls: every tile is
-  // then updated first and sketched after a barrier, once Ls is dead.  This
-  // keeps the kernel's LDS that of the offline-map flush (four workgroups per CU).
-  // Each tile's sketch columns go through the same per-wave block as X's
-  // (one after the other).
-  constexpr bool CM_ALIAS = P != 0 && LSZ >= 4 * 16 * XP;
-  __shared__ __align__(16) float cmXs[P != 0 && !CM_ALIAS ? 4 * 16 * XP : 4];
-  float* const cmX = CM_ALIAS ? Ls : cmXs;                 // [wave][16 values][16 keys]
+  // That scratch lives in the key staging Ls: every tile is updated first and
+  // sketched after a barrier, once Ls is dead.  This keeps the kernel's LDS that
+  // of the offline-map flush (four workgroups per CU at K = V = 128).  Each tile's
+  // sketch columns go through the same per-wave block as X's (one after the
+  // other).
+  static_assert(P == 0 || LSZ >= 4 * 16 * XP, "the transposed blocks must fit the key staging");
+  float* const cmX = Ls;                                   // [wave][16 values][16 keys]
   float* const cmU = cmX;                                  // [wave][16 values][16 sketch columns], before X's blocks
-  __shared__ __align__(16) float cmS[P == 0 ? 4 : LSZ >= 16 * K + 5 * R ? 24 : 24 + 5 * R];  // mu parts, R^{-1}/sqrt(mu) (L_G and w)
-  // F1 of the map, in its own LDS only where the key staging has no room
-  constexpr bool CMF_OWN = P > 0 && LSZ < P * K + 16 * RT * (P + 1);
-  __shared__ __align__(16) float cmF[CMF_OWN ? 16 * RT * (P + 1) : 4];
+  __shared__ __align__(16) float cmS[P == 0 ? 4 : 24];     // mu parts, R^{-1}/sqrt(mu)
   static_assert(!EXACT || (LSZ >= R * (K + 4) && SP * UP >= 2 * R * (R + 1)),
                 "the exact map's sums must fit the window staging");
   floatx4 nacc[P != 0 ? MT : 1];   // N^T (rows 4 lg + i: pivots a < 4, or every sketch column), this wave's values
@@ -1158,8 +1154,7 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
 
   if constexpr (P > 0) {
     if (want_U)
-      coef_map_tail<K, R, P, MT, RT, LSZ, SP * UP, SK>(a, item, wave, lane, tid, rh, nacc, gram, dsq, msq, Ls, Us,
-                                                                 cmS, OmL, cmF);
+      coef_map_tail<K, R, P, MT, RT, LSZ, SP * UP, SK>(a, item, wave, lane, tid, rh, nacc, gram, dsq, msq, Ls, Us, cmS, OmL);
   }
   if constexpr (EXACT) {
     if (want_U) coef_map_exact_tail<K, R, SK>(a, item, wave, lane, tid, rh, nacc, gacc, msq, Ls, Us, cmS);

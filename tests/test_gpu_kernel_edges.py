@@ -3,7 +3,7 @@ where they can go wrong, against the recurrence in 64 bits (plain torch)."""
 import pytest
 import torch
 
-from paper_2609_33051_amd import inputs
+from paper_2609_33051_amd import binding, inputs
 from paper_2609_33051_amd.layer import SketchSSMLayer
 
 pytestmark = pytest.mark.gpu
@@ -56,7 +56,7 @@ def test_flush_of_any_window(kind, K, V, W):
     om, C = (torch.as_tensor(x) for x in inputs.omega(wl))
     lay = SketchSSMLayer(kind, 2, 3, K, V, 16, W, "bf16", "cuda", S=S, omega=om, coef=C)
     lay.init_sketch()
-    for name in ("rk", "rv"):  # stale slots of an earlier window must not show
+    for name in ("rk", "rv"):  # slots not yet written must not show in the reads (the flush uses every slot)
         getattr(lay, name).fill_(float("nan"))
     X = S.double()
     for t in range(W):
@@ -66,6 +66,41 @@ def test_flush_of_any_window(kind, K, V, W):
     assert _rel(got, o) < REL
     assert _rel(lay.state(), X) < REL
     assert _rel(lay.sketch_matrix(), torch.stack([X[:, h] @ om[h].cuda().double() for h in range(3)], 1)) < REL
+
+
+@pytest.mark.parametrize("kind", ["mamba2", "gdn", "kda"])
+@pytest.mark.parametrize("K,V", [(64, 64), (128, 64), (128, 128)])
+@pytest.mark.parametrize("W,m", [(16, 1), (16, 5), (16, 13), (16, 16), (32, 15), (32, 16), (32, 17), (32, 18), (32, 27)])
+@pytest.mark.parametrize("pivots", [0, 4])
+def test_early_flush_ignores_unused_slots(kind, K, V, W, m, pivots):
+    """A window flushed after m tokens, with NaN in everything the flush has no
+    business with: ring slots m and on, and the rows of T^{-1} from slot m - 1
+    on, their diagonals and what lies above."""
+    wl = inputs.tiny(kind, batch=3, heads=3, dk=K, dv=V, rank=16, window=W, io="bf16")
+    S = inputs.initial_state(wl, "cuda")
+    om, C = (torch.as_tensor(x) for x in inputs.omega(wl))
+    lay = SketchSSMLayer(kind, 3, 3, K, V, 16, W, "bf16", "cuda", S=S, omega=om, coef=C, pivots=pivots)
+    lay.init_sketch()
+    X = S.double()
+    for t in range(m):
+        tok = inputs.step_inputs(wl, t, "cuda")
+        X, o = _step64(kind, X, tok)
+        if t < m - 1:
+            lay.step(tok)
+    lay.write_token(tok, m - 1)
+    for name in ("rk", "rv", "rbeta", "rla"):
+        getattr(lay, name)[:, :, m:] = float("nan")
+    if lay.rt is not None:
+        s, j = torch.meshgrid(torch.arange(W), torch.arange(W), indexing="ij")
+        unused = ((s >= m - 1) | (j >= s)).cuda()
+        lay.rt.permute(0, 3, 1, 2)[unused] = float("nan")  # [slot][column][H][B]
+    got = torch.empty_like(lay.o)
+    binding.sketchssm_update(lay.cfg, lay.S, lay.omega, lay.ring, m - 1, tok["q"], lay.U, got, lay.stream(), cmap=lay.cmap)
+    assert _rel(got, o) < REL
+    assert _rel(lay.state(), X) < REL
+    assert _rel(lay.sketch_matrix(), torch.stack([X[:, h] @ om[h].cuda().double() for h in range(3)], 1)) < REL
+    if pivots:
+        assert bool(torch.isfinite(lay.cmap).all())
 
 
 def test_kda_flush_that_forgets_a_channel():

@@ -210,11 +210,14 @@ typedef struct {
  * whose o overlaps q or the ring's inputs runs as a window of one token, at
  * the flush's speed.
  *
- * Occupancy: a flush with pivots = 0 and the single-token update launch with
- * unused dynamic LDS so that only a few of their workgroups are resident per
- * CU (by the bytes of an item's state), which streams the in-place state
- * faster than more would; other kernels on the device are not affected, except
- * that a kernel running concurrently on the same CUs finds that LDS taken.
+ * Occupancy: the single-token update and, with pivots = 0, the flushes of
+ * MAMBA2 (every shape) and of GDN and KDA at dk = dv = 128 launch with unused
+ * dynamic LDS so that only some of their workgroups are resident per CU (two to
+ * five of a flush, 32 or 40 KB of state of the single-token update), which
+ * streams the in-place state faster than more would (so does MAMBA2's flush with
+ * a map at dk = 128, dv = 64, rank 8, fp32 inputs); other kernels on the device
+ * are not affected, except that a kernel running concurrently on the same CUs
+ * finds that LDS taken.
  */
 int sketchssm_update(const skssm_config* cfg, float* S, const float* omega, const skssm_ring* ring,
                      int32_t n_buffered, const void* q, void* U, void* cmap, float* o, void* stream);

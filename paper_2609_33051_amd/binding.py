@@ -98,9 +98,12 @@ def ptr(x) -> int | None:
     """Device address of a tensor (or an int / None passed through)."""
     if x is None:
         return None
-    if isinstance(x, int):
-        return x
-    return x.data_ptr()
+    try:
+        return x.data_ptr()
+    except AttributeError:
+        if isinstance(x, int):
+            return x
+        raise
 
 
 def _dtype(x) -> int:
@@ -183,29 +186,33 @@ def prepare_full_read_baseline(cfg: Config, S, ring: Ring, n_buffered: int, q, o
 
 
 def sketchssm_update(cfg: Config, S, omega, ring: Ring | None, n_buffered: int, q, U, o, stream=None, cmap=None):
-    lib = load()
-    _check(lib.sketchssm_update(ctypes.byref(cfg), ptr(S), ptr(omega), ctypes.byref(ring) if ring else None,
-                                int(n_buffered), ptr(q), ptr(U), ptr(cmap), ptr(o), stream))
+    rc = (_lib or load()).sketchssm_update(cfg, ptr(S), ptr(omega), ring or None, int(n_buffered), ptr(q), ptr(U), ptr(cmap), ptr(o),
+                                 stream)
+    if rc:
+        _check(rc)
 
 
 def sketchssm_decode(cfg: Config, U, coef, ring: Ring, n_buffered: int, q, o, stream=None, cmap=None, S=None):
-    lib = load()
-    _check(lib.sketchssm_decode(ctypes.byref(cfg), ptr(U), ptr(coef), ptr(cmap), ptr(S),
-                                ctypes.byref(ring) if ring else None, int(n_buffered), ptr(q), ptr(o), stream))
+    rc = (_lib or load()).sketchssm_decode(cfg, ptr(U), ptr(coef), ptr(cmap), ptr(S), ring or None, int(n_buffered), ptr(q), ptr(o),
+                                 stream)
+    if rc:
+        _check(rc)
 
 
 def sketchssm_full_read_baseline(cfg: Config, S, ring: Ring, n_buffered: int, q, o, stream=None):
-    lib = load()
-    _check(lib.sketchssm_full_read_baseline(ctypes.byref(cfg), ptr(S), ctypes.byref(ring) if ring else None,
-                                            int(n_buffered), ptr(q), ptr(o), stream))
+    rc = (_lib or load()).sketchssm_full_read_baseline(cfg, ptr(S), ring or None, int(n_buffered), ptr(q), ptr(o), stream)
+    if rc:
+        _check(rc)
 
 
 def sketchssm_step(cfg: Config, baseline: bool, S, omega, coef, ring: Ring, n_buffered: int, k, v, beta, log_decay, q, U, o,
                    stream=None, cmap=None):
     """Append the token (k, v, beta, log_decay: its own arrays) to slot n_buffered and read it, in one launch."""
-    lib = load()
-    tok = Token(ptr(k), ptr(v), ptr(beta), ptr(log_decay))
-    rc = lib.sketchssm_step(cfg, 1 if baseline else 0, ptr(S), ptr(omega), ptr(coef), ring, n_buffered, tok, ptr(q), ptr(U),
+    try:
+        tok = Token(k, v, beta, log_decay)  # addresses
+    except TypeError:
+        tok = Token(ptr(k), ptr(v), ptr(beta), ptr(log_decay))
+    rc = (_lib or load()).sketchssm_step(cfg, 1 if baseline else 0, ptr(S), ptr(omega), ptr(coef), ring, n_buffered, tok, ptr(q), ptr(U),
                             ptr(cmap), ptr(o), stream)
     if rc:
         _check(rc)

@@ -528,17 +528,18 @@ __device__ __forceinline__ void rank_update(floatx4 (&x)[VTW][MT], int wave, int
 
 // What bounds it: the in-place stream of the state (8 K V bytes an item).  A GDN
 // item (K = V = 128, W = 16) alone on a CU takes 8.7 us from launch to end, 2.6
-// of them fp32 matrix-core time; before the channel work went to the matrix
-// cores it took 12.9, and B = 512 flushes (2.5 GB) went from 452 to 427 us (GDN)
-// and from 476 to 445 (KDA), the two-chunk W = 32 flush at B = 256 from 335 to
-// 266, and those with a P = 4 map from 517 to 472 (GDN) and 591 to 509 (KDA).
+// of them fp32 matrix-core time; with the channel work on the vector units it
+// took 12.9.  That move and the later state read (STATE_LATE, below) together
+// took B = 512 flushes (2.5 GB) from 452 to 427 us (GDN) and from 476 to 445
+// (KDA); the move alone the two-chunk W = 32 flush at B = 256 from 335 to 266 and
+// those with a P = 4 map from 517 to 472 (GDN) and 591 to 509 (KDA).
 //
 // Three workgroups per CU, or four for the state-dependent maps (P = 4 and
 // exact) at window 16 and rank <= 16: their flush spends part of each
 // workgroup's life off the memory bus (the map's products and algebra), so
-// occupancy pays there, even with the few registers the per-channel-decay
-// instances then spill.  (A bound of six for Mamba-2's at V = 64 spills 12 to 20
-// bytes: exact-map flush at B = 256 510 -> 543 us, P = 4 unchanged.)
+// occupancy pays there (within the bound's 128 registers only KDA's exact map at
+// rank 8 with a bf16 sketch spills, 8 bytes).  Mamba-2's at V = 64 need no bound:
+// 70 to 80 registers, six workgroups.
 template <int KIND, int K, int V, int R, int WMAX, typename IO, typename SK, int P>
 __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) void update_kernel(const UpdateArgs a) {
   constexpr bool ERASE = KIND != MAMBA2;
@@ -561,8 +562,8 @@ __global__ __launch_bounds__(256, (P != 0 && WMAX == 16 && R <= 16) ? 4 : 3) voi
   // shorten the dependent sums (and round less), two tiles' worth of four spill
   // where the map's bound leaves 128 registers (KDA, P = 4: 132 bytes per lane)
   // and where a window of two chunks holds the state through the second's
-  // staging (KDA, W = 32, rank 32, B = 256: 44 bytes and 422 us, with two
-  // chains 12 bytes and 397 us)
+  // staging (KDA, W = 32, rank 32, bf16 sketch, B = 256: 422 us, with two chains
+  // 397 and no spill)
   constexpr bool DEEP = (P == 0 && CH == 1) || VTW == 1;
   constexpr int NCW = DEEP ? 4 : 2;
   constexpr int NCU = DEEP ? 2 : 1;

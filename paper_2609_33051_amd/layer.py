@@ -29,6 +29,7 @@ into libsketchssm.so.  Buffers (caller-owned, as the ABI requires):
 from __future__ import annotations
 
 import torch
+from torch import Tensor
 
 from . import binding as B
 
@@ -89,7 +90,7 @@ class SketchSSMLayer:
                                 pi=self.rpi, tinv=self.rt)
         self.o = torch.zeros((Bt, H, V), dtype=f32, device=dev)
         self.n = 0  # slot of the next token in the current window
-        self._index, self._io = self.S.get_device(), iodt
+        self._index, self._io, self._nq, self._no = self.S.get_device(), iodt, Bt * H * K, Bt * H * V
         # what a token's tensors must be for step() to hand them to the kernels as they are
         self._token_like = tuple((name, t.dtype, tuple(t.shape[:2] + t.shape[3:])) for name, t in
                                  (("k", self.rk), ("v", self.rv), ("beta", self.rbeta), ("log_decay", self.rla)))
@@ -127,8 +128,18 @@ class SketchSSMLayer:
     def read(self, q: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tensor:
         """One decode token whose inputs already sit in ring slot n: a non-flush
         read (sketch, or exact full read for the baseline) while the window is
-        open, the flush on its W-th token."""
-        q, o = self._query(q), self._output(out)
+        open, the flush on its W-th token.  A q of another dtype or device, or
+        strided or broadcast, is read from a copy; `out` must be contiguous fp32
+        (ValueError)."""
+        if isinstance(q, Tensor) and (q.dtype is not self._io or not q.is_contiguous() or q.get_device() != self._index
+                                      or q.numel() < self._nq):
+            q = self._readable(q)
+        o = out
+        if o is None:
+            o = self.o
+        elif isinstance(o, Tensor) and (o.dtype is not torch.float32 or not o.is_contiguous()
+                                        or o.get_device() != self._index or o.numel() < self._no):
+            self._check_output(o)
         if self.n == self.window - 1:
             B.sketchssm_update(self.cfg, self.S, self.omega, self.ring, self.n, q, self.U, o, self.stream(),
                                cmap=self.cmap)
@@ -148,9 +159,11 @@ class SketchSSMLayer:
         the W calls n = 0..W-1 in order is the same as W calls of `read`; the
         caller owns that order (self.n is not touched).  The call keeps q's
         address, so a q that read() would copy is refused."""
-        if self._query(q) is not q:
+        if isinstance(q, Tensor) and self._readable(q) is not q:
             raise ValueError(f"q must be a contiguous {self._io} tensor [B][H][K] on {self.S.device}")
-        o = self._output(out)
+        o = self.o if out is None else out
+        if isinstance(o, Tensor):
+            self._check_output(o)
         st = self.stream()
         if n == self.window - 1:
             return B.prepare_update(self.cfg, self.S, self.omega, self.ring, n, q, self.U, o, st, cmap=self.cmap)
@@ -159,59 +172,63 @@ class SketchSSMLayer:
         return B.prepare_decode(self.cfg, self.U, self.coef, self.ring, n, q, o, st, cmap=self.cmap,
                                 S=self.S if self.dense_heads else None)
 
-    def _own_calls(self) -> bool:
-        """Whether write_token and read are this class's: an append or a read of
-        a subclass, or one set on the class or the instance, is called."""
-        cls, own = type(self), self.__dict__
-        return cls.write_token is _WRITE and cls.read is _READ and "write_token" not in own and "read" not in own
-
-    def _as_they_are(self, inp: dict) -> bool:
-        """Whether the token's update inputs are laid out as the kernels read them
-        (dtype, shape, contiguous, this device, 16-byte aligned)."""
+    def _addresses(self, inp: dict):
+        """The addresses of the token's update inputs where they are laid out as
+        the kernels read them (dtype, shape, contiguous, this device, 16-byte
+        aligned), else None."""
+        out, index = [], self._index
         for name, dtype, shape in self._token_like:
             t = inp[name]
-            if (t.dtype is not dtype or t.shape != shape or not t.is_contiguous() or t.get_device() != self._index
-                    or t.data_ptr() & 15):
-                return False
-        return True
-
-    def _query(self, q):
-        """q as the kernels read it: itself where it is [B][H][K] in the io dtype
-        on this device, contiguous (whatever its shape), else a copy (an int is
-        an address)."""
-        if isinstance(q, torch.Tensor) and (
-                q.dtype is not self._io or not q.is_contiguous() or q.get_device() != self._index
-                or q.numel() < self.batch * self.heads * self.dk):
-            return torch.empty((self.batch, self.heads, self.dk), dtype=self._io, device=self.S.device).copy_(q)
-        return q
-
-    def _output(self, out):
-        """The tensor o is written to: the layer's own, or `out`, which must be
-        able to hold it (a view cannot be copied back into)."""
-        if out is None:
-            return self.o
-        if isinstance(out, torch.Tensor) and (
-                out.dtype is not torch.float32 or not out.is_contiguous()
-                or out.numel() < self.batch * self.heads * self.dv
-                or (out.get_device() != self._index and not out.is_pinned())):
-            raise ValueError(f"out must be a contiguous fp32 tensor [B][H][V] on {self.S.device}")
+            p = t.data_ptr()
+            if t.dtype is not dtype or t.shape != shape or not t.is_contiguous() or t.get_device() != index or p & 15:
+                return None
+            out.append(p)
         return out
 
+    def _readable(self, q: Tensor) -> Tensor:
+        """q as the kernels read it: itself where it is [B][H][K] in the io dtype
+        on this device, contiguous (whatever its shape), else a copy."""
+        if q.dtype is self._io and q.is_contiguous() and q.get_device() == self._index and q.numel() >= self._nq:
+            return q
+        return torch.empty((self.batch, self.heads, self.dk), dtype=self._io, device=self.S.device).copy_(q)
+
+    def _check_output(self, out: Tensor):
+        """`out` must be able to hold o: contiguous fp32, [B][H][V], on this
+        device or in pinned host memory (a view cannot be copied back into)."""
+        if (out.dtype is not torch.float32 or not out.is_contiguous() or out.numel() < self._no
+                or (out.get_device() != self._index and not out.is_pinned())):
+            raise ValueError(f"out must be a contiguous fp32 tensor [B][H][V] on {self.S.device}")
+
     def step(self, inp: dict, out: torch.Tensor | None = None) -> torch.Tensor:
-        """write_token + read.  Where the token's tensors can be read as they
-        are, the append and the read are one launch (sketchssm_step); others
-        (another dtype or device, strided, broadcast) are copied into the slot
-        first, four copies before the read's launch.  A token of GDN at B = 1,
-        H = 32 takes 9 us as one launch against 26 us, of KDA at B = 48, H = 32
-        17 us against 29 us (the copies' launches and their second pass over the
-        token)."""
-        if not (self._own_calls() and self._as_they_are(inp)):
+        """write_token + read.  Where the token's k, v, beta and log decay can be
+        read as they are, the append and the read are one launch (sketchssm_step);
+        others (another dtype or device, strided, broadcast) are copied into the
+        slot first, four copies before the read's launch.  q and out are as in
+        read().  A token of GDN at B = 1, H = 32 takes 9 us as one launch against
+        26 us, of KDA at B = 48, H = 32 17 us against 29 us (the copies' launches
+        and their second pass over the token)."""
+        # an append or a read of a subclass, or one set on the class or the
+        # instance, is called
+        cls, own = type(self), self.__dict__
+        tok = None
+        if cls.write_token is _WRITE and cls.read is _READ and "write_token" not in own and "read" not in own:
+            tok = self._addresses(inp)
+        if tok is None:
             self.write_token(inp)
             return self.read(inp["q"], out)
-        q, o = self._query(inp["q"]), self._output(out)
+        q = inp["q"]  # (as in read())
+        if isinstance(q, Tensor) and (q.dtype is not self._io or not q.is_contiguous() or q.get_device() != self._index
+                                      or q.numel() < self._nq):
+            q = self._readable(q)
+        o = out
+        if o is None:
+            o = self.o
+        elif isinstance(o, Tensor) and (o.dtype is not torch.float32 or not o.is_contiguous()
+                                        or o.get_device() != self._index or o.numel() < self._no):
+            self._check_output(o)
         n = self.n
-        B.sketchssm_step(self.cfg, self.baseline, self.S, self.omega, self.coef, self.ring, n, inp["k"], inp["v"],
-                         inp["beta"], inp["log_decay"], q, self.U, o, self.stream(), cmap=self.cmap)
+        B.sketchssm_step(self.cfg, self.baseline, self.S, self.omega, self.coef, self.ring, n, *tok, q, self.U, o,
+                         self.stream(), cmap=self.cmap)
         self.n = 0 if n == self.window - 1 else n + 1
         return o
 

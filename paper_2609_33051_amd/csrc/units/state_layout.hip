@@ -12,11 +12,6 @@
 // whole of what the wave holds, in flight only briefly.  Reading the row side
 // straight in the tiles' order (16 pieces of 64 bytes a load) moved 2 GiB at
 // 4.6 TB/s.
-//
-// The reads are non-temporal where the two arrays exceed the 256 MB last-level
-// cache, ordinary where they fit it (a prompt's states may still lie there): K =
-// V = 128, non-temporal / ordinary, states of 64 MiB 22.8 / 20.1 us, 128 MiB
-// 40.5 / 39.0, 256 MiB 77.1 / 96.8, 1 GiB 381 / 387.
 #include <hip/hip_runtime.h>
 
 #include "../args.h"
@@ -24,7 +19,7 @@
 
 namespace skssm {
 
-template <int K, bool TO_TILES, bool NT>
+template <int K, bool TO_TILES>
 __global__ __launch_bounds__(64) void state_layout_kernel(const float4* src, float4* dst) {
   constexpr int N = K / 16, KQ = K / 4;  // float4s per lane; float4s per row
   __shared__ float4 buf[16 * KQ];
@@ -32,7 +27,7 @@ __global__ __launch_bounds__(64) void state_layout_kernel(const float4* src, flo
   const size_t base = (size_t)blockIdx.x * (16 * KQ);
   float4 x[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) x[i] = NT ? ld_nt(src + base + 64 * i + lane) : src[base + 64 * i + lane];
+  for (int i = 0; i < N; ++i) x[i] = ld_nt(src + base + 64 * i + lane);
   // LDS holds the stripe in tile order with the low three bits of the position
   // exchanged by the channel group's, so that both sides hit different banks
 #pragma unroll
@@ -60,27 +55,18 @@ __global__ __launch_bounds__(64) void state_layout_kernel(const float4* src, flo
   }
 }
 
-template <int K, bool TO_TILES>
-void launch_layout(const float4* src, float4* dst, size_t stripes, hipStream_t s) {
-  const dim3 grid((unsigned)stripes);  // < 2^26 (the ABI bounds the items)
-  if (stripes * (64 * K) > ((size_t)128 << 20))
-    hipLaunchKernelGGL((state_layout_kernel<K, TO_TILES, true>), grid, dim3(64), 0, s, src, dst);
-  else
-    hipLaunchKernelGGL((state_layout_kernel<K, TO_TILES, false>), grid, dim3(64), 0, s, src, dst);
-}
-
 int run_state_layout(const float* src, float* dst, size_t items, int K, int V, int to_tiles, void* stream) {
   if ((K != 64 && K != 128) || V % 16) return -2;
-  const size_t stripes = items * (size_t)(V / 16);
+  const dim3 grid((unsigned)(items * (size_t)(V / 16)));  // < 2^26 (the ABI bounds the items)
   hipStream_t s = static_cast<hipStream_t>(stream);
   const float4* a = reinterpret_cast<const float4*>(src);
   float4* b = reinterpret_cast<float4*>(dst);
   if (K == 128) {
-    if (to_tiles) launch_layout<128, true>(a, b, stripes, s);
-    else launch_layout<128, false>(a, b, stripes, s);
+    if (to_tiles) hipLaunchKernelGGL((state_layout_kernel<128, true>), grid, dim3(64), 0, s, a, b);
+    else hipLaunchKernelGGL((state_layout_kernel<128, false>), grid, dim3(64), 0, s, a, b);
   } else {
-    if (to_tiles) launch_layout<64, true>(a, b, stripes, s);
-    else launch_layout<64, false>(a, b, stripes, s);
+    if (to_tiles) hipLaunchKernelGGL((state_layout_kernel<64, true>), grid, dim3(64), 0, s, a, b);
+    else hipLaunchKernelGGL((state_layout_kernel<64, false>), grid, dim3(64), 0, s, a, b);
   }
   return 0;
 }

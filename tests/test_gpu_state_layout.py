@@ -34,9 +34,9 @@ def test_state_layout_matches_definition(Bt, H, K, V):
 
 
 def test_state_layout_large_grid():
-    """More float4s than one pass of the launch grid covers (grid-stride loop)."""
-    Bt, H, K, V = 64, 32, 128, 128          # 2^25 floats: 8.4M float4s over at most 16384 x 256 threads
-    print(f"[case] state layout grid-stride B={Bt} H={H}", flush=True)
+    """16,384 stripes of 16 rows, one workgroup each."""
+    Bt, H, K, V = 64, 32, 128, 128
+    print(f"[case] state layout B={Bt} H={H}", flush=True)
     cfg = B.make_config("kda", Bt, H, K, V, 16, 16, "bf16")
     X = torch.randn((Bt, H, V, K), device="cuda", generator=torch.Generator(device="cuda").manual_seed(5))
     T = torch.empty((Bt, H, V * K), device="cuda")

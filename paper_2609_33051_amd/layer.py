@@ -91,9 +91,8 @@ class SketchSSMLayer:
         self.o = torch.zeros((Bt, H, V), dtype=f32, device=dev)
         self.n = 0  # slot of the next token in the current window
         self._index, self._io, self._nq, self._no = self.S.get_device(), iodt, Bt * H * K, Bt * H * V
-        # what a token's tensors must be for step() to hand them to the kernels as they are
-        self._token_like = tuple((name, t.dtype, tuple(t.shape[:2] + t.shape[3:])) for name, t in
-                                 (("k", self.rk), ("v", self.rv), ("beta", self.rbeta), ("log_decay", self.rla)))
+        # the shapes a token's tensors have where step() hands them to the kernel as they are
+        self._shapes = (Bt, H, K), (Bt, H, V), (Bt, H), (Bt, H, K) if kind == "kda" else (Bt, H)
 
     def sketch_matrix(self) -> torch.Tensor:
         """The sketch as [B][H][V][r] (a copy; U itself is stored in panels)."""
@@ -176,14 +175,17 @@ class SketchSSMLayer:
         """The addresses of the token's update inputs where they are laid out as
         the kernels read them (dtype, shape, contiguous, this device, 16-byte
         aligned), else None."""
-        out, index = [], self._index
-        for name, dtype, shape in self._token_like:
-            t = inp[name]
-            p = t.data_ptr()
-            if t.dtype is not dtype or t.shape != shape or not t.is_contiguous() or t.get_device() != index or p & 15:
-                return None
-            out.append(p)
-        return out
+        k, v, beta, decay = inp["k"], inp["v"], inp["beta"], inp["log_decay"]
+        io, f32 = self._io, torch.float32
+        ks, vs, bs, ds = self._shapes
+        if (k.dtype is io and v.dtype is io and beta.dtype is f32 and decay.dtype is f32
+                and k.shape == ks and v.shape == vs and beta.shape == bs and decay.shape == ds
+                and k.is_contiguous() and v.is_contiguous() and beta.is_contiguous() and decay.is_contiguous()
+                and self._index == k.get_device() == v.get_device() == beta.get_device() == decay.get_device()):
+            at = k.data_ptr(), v.data_ptr(), beta.data_ptr(), decay.data_ptr()
+            if not (at[0] | at[1] | at[2] | at[3]) & 15:
+                return at
+        return None
 
     def _readable(self, q: Tensor) -> Tensor:
         """q as the kernels read it: itself where it is [B][H][K] in the io dtype
@@ -227,8 +229,9 @@ class SketchSSMLayer:
                                         or o.get_device() != self._index or o.numel() < self._no):
             self._check_output(o)
         n = self.n
-        B.sketchssm_step(self.cfg, self.baseline, self.S, self.omega, self.coef, self.ring, n, *tok, q, self.U, o,
-                         self.stream(), cmap=self.cmap)
+        k, v, beta, decay = tok
+        B.sketchssm_step(self.cfg, self.baseline, self.S, self.omega, self.coef, self.ring, n, k, v, beta, decay, q, self.U,
+                         o, self.stream(), self.cmap)
         self.n = 0 if n == self.window - 1 else n + 1
         return o
 
